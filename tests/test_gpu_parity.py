@@ -512,6 +512,37 @@ def test_prefill_importance_matches_oracle(name, shape):
             np.testing.assert_array_equal(m[h], oracle.select(got[h], None, T, kh, W, initial=True))
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,grow", [
+    # one, two and four waves per 64 rows (grids of >= 768, >= 192 and fewer
+    # 256-row blocks), at the edges of the 32-row tiles, of the 64- and
+    # 128-row LDS tiles and of the 64-, 128- and 256-row blocks
+    (1, 2, 2, 31, 0.0), (1, 2, 2, 32, 0.0), (1, 2, 1, 33, 0.0), (1, 4, 2, 64, 0.0), (1, 4, 1, 65, 0.0),
+    (1, 3, 3, 127, 0.0), (1, 2, 2, 128, 0.0), (1, 2, 2, 129, 0.0), (1, 9, 9, 257, 0.0), (1, 8, 1, 385, 0.0),
+    (2, 96, 12, 129, 0.0), (4, 48, 12, 256, 0.0), (2, 64, 32, 513, 0.0),
+    (8, 96, 96, 63, 0.0), (4, 200, 25, 257, 0.0), (8, 48, 48, 449, 0.0), (16, 96, 96, 700, 0.0),
+    # keys that grow along the prompt: the running maxima are raised all the way
+    (1, 2, 2, 700, 1.0), (8, 48, 48, 449, 1.0),
+])
+def test_prefill_importance_tile_edges(B, Hq, Hkv, T, grow):
+    """Prompt importance against the fp64 oracle where its tiling can go
+    wrong, on the first, a middle and the last head; same bound as above."""
+    dev = _dev()
+    g = torch.Generator(device=dev)
+    g.manual_seed(T)
+    k = torch.randn(B, Hkv, T, 128, generator=g, device=dev)
+    k *= 1.0 + grow * torch.arange(T, device=dev)[:, None] / 16
+    k, q = k.half(), torch.randn(B, Hq, T, 128, generator=g, device=dev).half()
+    got = torch.full((B, Hkv, T), float("nan"), dtype=torch.float32, device=dev)
+    mikv.mikv_prefill_importance(q, k, got, SCALE)
+    torch.cuda.synchronize()
+    NH, G = B * Hkv, Hq // Hkv
+    mass = got.double().sum(-1).cpu().numpy().reshape(NH)
+    np.testing.assert_allclose(mass, G * T, rtol=1e-4)
+    for h in sorted({0, NH // 2, NH - 1}):
+        ref = oracle.prefill_importance(np16(q.reshape(NH, G, T, 128)[h]), np16(k.reshape(NH, T, 128)[h]), SCALE)
+        np.testing.assert_allclose(got.reshape(NH, T)[h].cpu().numpy(), ref, rtol=1e-4, atol=1e-6, err_msg=f"head {h}")
+
+
 def test_lockstep_with_prompt_importance():
     """A decode run whose first selection uses the prompt's own H2O scores
     (mikv_prefill_importance) instead of seeded ones: the oracle takes the
