@@ -193,69 +193,71 @@ __global__ __launch_bounds__(kChunk) void count_hi_kernel(const uint8_t *hi_mask
   }
 }
 
+// Sum of counts[0 .. n), by one wave (the result in every lane).
+__device__ inline int wave_count(const int32_t *counts, int n) {
+  int v = 0;
+  for (int c = threadIdx.x & 63; c < n; c += 64) v += counts[c];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
 // Place tokens [chunk*kChunk, ...) of head blockIdx.y.  With `counts`
 // (mask given) slots come from the per-chunk counts and an in-block scan;
 // without, every token goes to the importance pool in order.  When `commit`
 // is set (a single chunk per head), the block also advances n_hi/n_lo.
+//
+// The rows are quantized pool by pool, keys then values, so that a wave runs
+// one format (a wave over neighbouring tokens nearly always held both pools,
+// and ran both encoders for all its rows).  Bound: the stream of fp16 rows and
+// codes, now that a value costs some ten VALU instructions (encode32): 1280
+// heads x 8192 tokens, INT8 + INT2 2254 -> 1637 us (4.2 TB/s of rows read and
+// codes written), 128 x 32768, fp16 + INT2 661 -> 593 us (4.6 TB/s), 128 x
+// 16384, GQA 535 -> 338 us.
 template <int HI_BITS, int LO_BITS>
 __global__ __launch_bounds__(256) void place_kernel(Pools P, const uint16_t *k, const uint16_t *v,
                                                     const float *balance, int pos0, int n,
                                                     const uint8_t *hi_mask, const float *score_init,
                                                     const int32_t *counts, int nchunks, int commit) {
   const int h = blockIdx.y, chunk = blockIdx.x, tid = threadIdx.x;
-  __shared__ int s_slot[kChunk];
-  __shared__ uint8_t s_hi[kChunk];
+  __shared__ int s_slot[kChunk];       // by order: retained-pool tokens first
+  __shared__ uint8_t s_token[kChunk];  // order -> token of the chunk
   __shared__ int s_wave[kChunk / 64][2];
-  __shared__ int s_base[2];
-  __shared__ int s_total[2];
+  __shared__ int s_before;
   const int j0 = chunk * kChunk;
   const int cnt = min(kChunk, n - j0);
   const int n_hi0 = P.n_hi[h], n_lo0 = P.n_lo[h];
 
   // --- slot assignment -------------------------------------------------
-  int j = j0 + tid;
+  const int j = j0 + tid;
+  const int live = tid < cnt;
   int is_hi = 1;
-  if (hi_mask) is_hi = (tid < cnt && hi_mask[(int64_t)h * n + j]) ? 1 : 0;
-  int live = tid < cnt;
-  unsigned long long bh = __ballot(live && is_hi);
-  unsigned long long bl = __ballot(live && !is_hi);
-  unsigned long long below = (1ull << (tid & 63)) - 1ull;
+  if (hi_mask) is_hi = (live && hi_mask[(int64_t)h * n + j]) ? 1 : 0;
+  const unsigned long long bh = __ballot(live && is_hi);
+  const unsigned long long bl = __ballot(live && !is_hi);
+  const unsigned long long below = (1ull << (tid & 63)) - 1ull;
   int r_hi = __popcll(bh & below), r_lo = __popcll(bl & below);
   if ((tid & 63) == 0) {
     s_wave[tid >> 6][0] = __popcll(bh);
     s_wave[tid >> 6][1] = __popcll(bl);
   }
-  if (tid == 0) {
-    int bhi = 0, blo = 0;
-    if (counts) {
-      for (int c = 0; c < chunk; ++c) {
-        int ch = counts[h * nchunks + c];
-        bhi += ch;
-        blo += kChunk - ch;
-      }
-    } else {
-      bhi = j0;
-    }
-    s_base[0] = n_hi0 + bhi;
-    s_base[1] = n_lo0 + blo;
+  if (tid < 64) {
+    const int before = counts ? wave_count(counts + (int64_t)h * nchunks, chunk) : j0;
+    if (tid == 0) s_before = before;
   }
   __syncthreads();
-  if (tid == 0) {
-    int th = 0, tl = 0;
-    for (int w = 0; w < kChunk / 64; ++w) {
-      th += s_wave[w][0];
-      tl += s_wave[w][1];
+  int cnt_hi = 0, cnt_lo = 0;
+  for (int w = 0; w < kChunk / 64; ++w) {
+    if (w < (tid >> 6)) {
+      r_hi += s_wave[w][0];
+      r_lo += s_wave[w][1];
     }
-    s_total[0] = th;
-    s_total[1] = tl;
-  }
-  for (int w = 0; w < (tid >> 6); ++w) {
-    r_hi += s_wave[w][0];
-    r_lo += s_wave[w][1];
+    cnt_hi += s_wave[w][0];
+    cnt_lo += s_wave[w][1];
   }
   if (live) {
-    int slot = is_hi ? s_base[0] + r_hi : s_base[1] + r_lo;
-    int cap = is_hi ? P.cap_hi : P.cap_lo;
+    int slot = is_hi ? n_hi0 + s_before + r_hi : n_lo0 + (j0 - s_before) + r_lo;
+    const int cap = is_hi ? P.cap_hi : P.cap_lo;
     if (!is_hi && P.evict) {
       slot = -1;  // evicted: stored nowhere (the map says "not in the importance pool")
     } else if (!is_hi && P.lo_kb &&
@@ -268,9 +270,10 @@ __global__ __launch_bounds__(256) void place_kernel(Pools P, const uint16_t *k, 
       atomicOr(P.status, is_hi ? MIKV_DEVERR_HI_FULL : MIKV_DEVERR_LO_FULL);
       slot = -1;
     }
-    s_slot[tid] = slot;
-    s_hi[tid] = (uint8_t)is_hi;
-    int pos = pos0 + j;
+    const int o = is_hi ? cnt_lo + r_hi : r_lo;
+    s_slot[o] = slot;
+    s_token[o] = (uint8_t)tid;
+    const int pos = pos0 + j;
     if (slot >= 0) {
       if (is_hi) {
         P.hi_pos[(int64_t)h * P.cap_hi + slot] = pos;
@@ -285,77 +288,77 @@ __global__ __launch_bounds__(256) void place_kernel(Pools P, const uint16_t *k, 
   }
   __syncthreads();
 
-  // --- quantize / store rows: 4 lanes per row, rows = (token, K|V) ------
+  // --- quantize / store rows: 4 lanes per row --------------------------
   const int lane4 = tid & 3;
   const int ng = kHeadDim / P.group;
-  for (int r = tid >> 2; r < 2 * cnt; r += 256 / 4) {
-    const int t = r >> 1, is_v = r & 1;
-    const int slot = s_slot[t];
-    const int hi = s_hi[t];
-    const int64_t src_row = (int64_t)h * n + j0 + t;
-    const uint16_t *src = (is_v ? v : k) + src_row * kHeadDim + lane4 * 32;
-    const float *bal = (!is_v && balance) ? balance + (int64_t)h * kHeadDim + lane4 * 32 : nullptr;
+  // row r of `m` tokens from order o0 on: keys, then values
+  auto load = [&](int r, int o0, int m, bool &is_v, int &t, int &slot, float x[32]) {
+    is_v = r >= m;
+    const int o = o0 + (is_v ? r - m : r);
+    t = s_token[o];
+    slot = s_slot[o];
+    const uint16_t *src = (is_v ? v : k) + ((int64_t)h * n + j0 + t) * kHeadDim + lane4 * 32;
+    load_row_segment(src, !is_v && balance ? balance + (int64_t)h * kHeadDim + lane4 * 32 : nullptr, x);
+  };
+  for (int r = tid >> 2; r < (P.evict ? 0 : 2 * cnt_lo); r += 256 / 4) {
+    bool is_v;
+    int t, slot;
     float x[32];
-    load_row_segment(src, bal, x);
+    load(r, 0, cnt_lo, is_v, t, slot, x);
     // every lane of a group must take part in the shuffles: no early exit
     const bool store = slot >= 0;
-    const int sl = store ? slot : 0;
-    if (hi) {
-      if (HI_BITS == 16) {
-        if (store) {
-          uint8_t *dst = (is_v ? P.hi_v : P.hi_k) + (((int64_t)h * P.cap_hi + sl) * kHeadDim + lane4 * 32) * 2;
-          uint32_t w[16];
-#pragma unroll
-          for (int c = 0; c < 16; ++c)
-            w[c] = pack_f16x2(x[2 * c], x[2 * c + 1]);
-          uint4 *d4 = reinterpret_cast<uint4 *>(dst);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) d4[i] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
-        }
-      } else {
-        uint8_t *dst = (is_v ? P.hi_v : P.hi_k) + ((int64_t)h * P.cap_hi + sl) * (kHeadDim * HI_BITS / 8) +
-                       lane4 * (32 * HI_BITS / 8);
-        uint32_t *par = (is_v ? P.hi_vp : P.hi_kp) + ((int64_t)h * P.cap_hi + sl) * ng + (lane4 * 32) / P.group;
-        quantize_segment<HI_BITS>(x, P.group, lane4, dst, par, store);
-      }
-    } else if (P.evict) {
-      // evicted token (no retained pool): nothing to store; the four lanes
-      // of the row take this branch together
-    } else if (LO_BITS == 2 && is_v && P.v_tiled) {
+    const int64_t row = (int64_t)h * P.cap_lo + (store ? slot : 0);
+    if (LO_BITS == 2 && is_v && P.v_tiled) {
       // 2-bit values of a GQA cache go to the tiled layout, byte by byte
       uint32_t w[2];
       GroupParams gp = quantize_words<2>(x, P.group, w);
       if (store) {
-        store_int2_v(P.lo_v + (int64_t)h * P.cap_lo * (kHeadDim / 4), sl, lane4, w);
+        store_int2_v(P.lo_v + (int64_t)h * P.cap_lo * (kHeadDim / 4), slot, lane4, w);
         if ((lane4 % (P.group / 32)) == 0)
-          P.lo_vp[((int64_t)h * P.cap_lo + sl) * ng + (lane4 * 32) / P.group] =
-              (uint32_t)gp.a16 | ((uint32_t)gp.b16 << 16);
+          P.lo_vp[row * ng + (lane4 * 32) / P.group] = (uint32_t)gp.a16 | ((uint32_t)gp.b16 << 16);
       }
     } else if (!is_v && P.lo_kb) {
       // per-channel key: codes with its block's parameters (the block is
-      // complete: the placement below refused tokens of incomplete blocks)
+      // complete: the placement above refused tokens of incomplete blocks)
       if (store) {
         uint32_t w[LO_BITS];
         const int blk = (pos0 + j0 + t) / kKeyBlock;
         encode_key_channels<LO_BITS>(x, P.lo_kb + ((int64_t)h * P.n_kblk + blk) * kHeadDim, lane4, w);
-        uint32_t *dst = reinterpret_cast<uint32_t *>(P.lo_k + ((int64_t)h * P.cap_lo + sl) * (kHeadDim * LO_BITS / 8) +
-                                                     lane4 * (32 * LO_BITS / 8));
+        uint32_t *dst = reinterpret_cast<uint32_t *>(P.lo_k + row * (kHeadDim * LO_BITS / 8) + lane4 * (32 * LO_BITS / 8));
 #pragma unroll
         for (int i = 0; i < LO_BITS; ++i) dst[i] = w[i];
       }
     } else {
-      uint8_t *dst = (is_v ? P.lo_v : P.lo_k) + ((int64_t)h * P.cap_lo + sl) * (kHeadDim * LO_BITS / 8) +
-                     lane4 * (32 * LO_BITS / 8);
-      uint32_t *par = (is_v ? P.lo_vp : P.lo_kp) + ((int64_t)h * P.cap_lo + sl) * ng + (lane4 * 32) / P.group;
-      quantize_segment<LO_BITS>(x, P.group, lane4, dst, par, store);
+      uint8_t *dst = (is_v ? P.lo_v : P.lo_k) + row * (kHeadDim * LO_BITS / 8) + lane4 * (32 * LO_BITS / 8);
+      quantize_segment<LO_BITS>(x, P.group, lane4, dst, (is_v ? P.lo_vp : P.lo_kp) + row * ng + (lane4 * 32) / P.group,
+                                store);
     }
   }
-  if (commit) {
-    __syncthreads();
-    if (tid == 0) {
-      P.n_hi[h] = min(n_hi0 + s_total[0], P.cap_hi);
-      if (!P.evict) P.n_lo[h] = min(n_lo0 + s_total[1], P.cap_lo);
+  for (int r = tid >> 2; r < 2 * cnt_hi; r += 256 / 4) {
+    bool is_v;
+    int t, slot;
+    float x[32];
+    load(r, cnt_lo, cnt_hi, is_v, t, slot, x);
+    const bool store = slot >= 0;
+    const int64_t row = (int64_t)h * P.cap_hi + (store ? slot : 0);
+    if (HI_BITS == 16) {
+      if (store) {
+        uint4 *d4 = reinterpret_cast<uint4 *>((is_v ? P.hi_v : P.hi_k) + (row * kHeadDim + lane4 * 32) * 2);
+        uint32_t w[16];
+#pragma unroll
+        for (int c = 0; c < 16; ++c) w[c] = pack_f16x2(x[2 * c], x[2 * c + 1]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d4[i] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
+      }
+    } else {
+      uint8_t *dst = (is_v ? P.hi_v : P.hi_k) + row * (kHeadDim * HI_BITS / 8) + lane4 * (32 * HI_BITS / 8);
+      quantize_segment<HI_BITS>(x, P.group, lane4, dst, (is_v ? P.hi_vp : P.hi_kp) + row * ng + (lane4 * 32) / P.group,
+                                store);
     }
+  }
+  if (commit && tid == 0) {  // (every thread read the counts before the barriers above)
+    P.n_hi[h] = min(n_hi0 + cnt_hi, P.cap_hi);
+    if (!P.evict) P.n_lo[h] = min(n_lo0 + cnt_lo, P.cap_lo);
   }
 }
 
@@ -379,19 +382,16 @@ __global__ __launch_bounds__(64) void append_one_kernel(Pools P, const uint16_t 
   }
 }
 
-// Advance n_hi/n_lo after a multi-chunk placement.
-__global__ void commit_counts_kernel(Pools P, int n_heads, int n, const int32_t *counts, int nchunks) {
-  int h = blockIdx.x * blockDim.x + threadIdx.x;
+// Advance n_hi/n_lo after a multi-chunk placement: one wave per head.
+__global__ __launch_bounds__(256) void commit_counts_kernel(Pools P, int n_heads, int n, const int32_t *counts,
+                                                            int nchunks) {
+  const int h = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (h >= n_heads) return;
-  int th = n;
-  int tl = 0;
-  if (counts) {
-    th = 0;
-    for (int c = 0; c < nchunks; ++c) th += counts[h * nchunks + c];
-    tl = n - th;
+  const int th = counts ? wave_count(counts + (int64_t)h * nchunks, nchunks) : n;
+  if ((threadIdx.x & 63) == 0) {
+    P.n_hi[h] = min(P.n_hi[h] + th, P.cap_hi);
+    if (!P.evict) P.n_lo[h] = min(P.n_lo[h] + (n - th), P.cap_lo);
   }
-  P.n_hi[h] = min(P.n_hi[h] + th, P.cap_hi);
-  if (!P.evict) P.n_lo[h] = min(P.n_lo[h] + tl, P.cap_lo);
 }
 
 template <int HI_BITS, int LO_BITS>
@@ -419,7 +419,7 @@ void launch_place(const mikv_cache *c, const uint16_t *k, const uint16_t *v, con
   hipLaunchKernelGGL((place_kernel<HI_BITS, LO_BITS>), dim3(nchunks, NH), dim3(256), 0, st, P, k, v, balance,
                      pos0, n, hi_mask, score_init, hi_mask ? counts : nullptr, nchunks, commit);
   if (!commit) {
-    hipLaunchKernelGGL(commit_counts_kernel, dim3((NH + 255) / 256), dim3(256), 0, st, P, NH, n,
+    hipLaunchKernelGGL(commit_counts_kernel, dim3((NH + 3) / 4), dim3(256), 0, st, P, NH, n,
                        hi_mask ? counts : nullptr, nchunks);
   }
 }
