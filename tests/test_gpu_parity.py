@@ -115,6 +115,28 @@ def test_select_prefill_matches_oracle(L, k, W):
         np.testing.assert_array_equal(got[h], oracle.select(sc[h], None, L, k, W, initial=True))
 
 
+@pytest.mark.parametrize("L,k,W", [(4096, 900, 1), (4097, 1, 1), (16384, 16000, 7), (16385, 5000, 0),
+                                   (32768, 3000, 0), (32800, 32799, 0), (2, 1, 0), (1025, 512, 0)])
+def test_select_prefill_digit_edges(L, k, W):
+    """First selection where its registers, digits and early end can go wrong:
+    all scores equal (only the position digits tell), scores that differ in
+    the last bit, negative and zero scores, one score far above the rest."""
+    dev = _dev()
+    rng = np.random.default_rng(L)
+    sc = np.ones((5, L), np.float32)
+    sc[1] = (0x3F800000 + rng.integers(0, 4, L)).astype(np.uint32).view(np.float32)
+    sc[2] = -rng.random(L).astype(np.float32) * (rng.random(L) < 0.5)
+    sc[3] = 0.0
+    sc[3, L // 2] = 1e30
+    sc[4] = (rng.random(L) ** 8).astype(np.float32)
+    mask = torch.empty(5, L, dtype=torch.uint8, device=dev)
+    mikv.mikv_select_prefill(torch.from_numpy(sc).to(dev), k, W, mask)
+    torch.cuda.synchronize()
+    got = mask.cpu().numpy().astype(bool)
+    for h in range(5):
+        np.testing.assert_array_equal(got[h], oracle.select(sc[h], None, L, k, W, initial=True), err_msg=f"head {h}")
+
+
 # -- lock-step decode ------------------------------------------------------------------
 
 SMALL = {
