@@ -346,9 +346,11 @@ __device__ void attn_chunk(const AttnArgs &A, int h, int chunk, int rec_chunk, b
   }
 
   constexpr int kPerIter = kWaves * TPW * UNROLL;
-  // chunks are whole multiples of 128 tokens, at most max_chunk(G): an
-  // iteration never runs past the LDS score buffer
+  // chunks are whole iterations, at most max_chunk(G) tokens (multiples of
+  // 128, or the shorter ones of make_plan from G = 4 on): an iteration never
+  // runs past the LDS score buffer
   static_assert(128 % kPerIter == 0 && max_chunk(G) % 128 == 0, "iteration must divide 128 tokens");
+  static_assert(G < 4 || kPerIter <= 16 || (BITS <= 4 && kPerIter <= 32), "and from G = 4 on the chunks of make_plan");
   constexpr int kSeg = Rows<BITS, CPL>::KW * 4;  // bytes loaded per lane's row segment
   // byte offset of the lane's segment in a row, and the bit shift that
   // aligns it (non-zero only for 3-bit segments of 48 or 24 bits, which
@@ -1715,6 +1717,14 @@ int round_up(int64_t x, int m) { return (int)(((x + m - 1) / m) * m); }
 std::atomic<int64_t> g_resident_bytes{kResidentBytes};
 int64_t resident_budget() { return g_resident_bytes.load(std::memory_order_relaxed); }
 
+size_t workspace_bytes_for(const mikv_cache *c, const Plan &p) {
+  const int64_t BQ = (int64_t)c->batch * c->q_heads;
+  return (size_t)(BQ * (p.nc_hi + p.nc_lo) * kRec * 4 + BQ * c->cap_hi * 4);
+}
+
+constexpr int64_t kFewWaves = 2048;
+constexpr size_t kFewWorkspace = (size_t)16 << 20;
+
 // size_bound: the plan with the most chunks the resident share can give
 // (workspaces are sized from it, so a workspace stays large enough when the
 // share changes).
@@ -1746,18 +1756,38 @@ Plan make_plan(const mikv_cache *c, int length, bool size_bound = false) {
   const int64_t target_hi = group_size_of(c) == 1 ? target * hi_scale : target;
   p.chunk_hi = std::min(cmax, std::max(128, round_up(target_hi / bh, 128)));
   p.chunk_lo = std::min(cmax, std::max(128, round_up(target / bl, 128)));
-  p.nc_hi = std::max(1, (span_hi + p.chunk_hi - 1) / p.chunk_hi);
-  p.nc_lo = evicting(c) ? 0 : std::max(1, (span_lo + p.chunk_lo - 1) / p.chunk_lo);
+  auto chunks = [&]() {
+    p.nc_hi = std::max(1, (span_hi + p.chunk_hi - 1) / p.chunk_hi);
+    p.nc_lo = evicting(c) ? 0 : std::max(1, (span_lo + p.chunk_lo - 1) / p.chunk_lo);
+  };
+  chunks();
+  // From four query heads per KV head on, a wave takes two (G = 8: four) times
+  // as many iterations for an importance-pool chunk as for a retained-pool one,
+  // and while the waves all fit the chip at once (kFewWaves: two per SIMD) the
+  // longest of them is the launch.  Then shorter chunks: retained pool 128
+  // tokens while that many waves are free, importance pool down to 32 as long
+  // as the waves still fit.  Measured (us per attention, before -> after):
+  // 1 sequence x 64/8 heads x 4096 tokens 31.4 -> 19.3, 4 x 64/8 x 7001 50.1 ->
+  // 31.6 (36.8 in 16 % more waves than fit), 1 x 32/8 x 4096 17.2 -> 13.8, 4 x
+  // 32/8 x 4096 19.3 -> 16.8; with one query head shorter chunks gain nothing
+  // (1 x 40 x 5003: 15.2 -> 16.6).
+  const int64_t base = NH * (p.nc_hi + p.nc_lo);
+  if (group_size_of(c) >= 4 && base < kFewWaves) {
+    const Plan wide = p;
+    if (2 * base <= kFewWaves && p.nc_lo) p.chunk_lo = std::min(p.chunk_lo, 128);
+    const int step = c->hi_bits == 4 ? 32 : 16;  // whole iterations
+    for (p.chunk_hi = 32;; p.chunk_hi += step) {
+      chunks();
+      if (p.chunk_hi >= wide.chunk_hi || NH * (p.nc_hi + p.nc_lo) <= kFewWaves) break;
+    }
+    // (a workspace that a caller's scratch of a fixed size held before still does)
+    if (NH * (p.nc_hi + p.nc_lo) > kFewWaves || workspace_bytes_for(c, p) > kFewWorkspace) p = wide;
+  }
   // every token is in one of the pools, so at least length - cap_hi are in
   // the retained one (only the dispatch order depends on this)
   const int lo_min = std::max(0, std::min(span_lo, length - c->cap_hi));
   p.nc_first = p.nc_hi + std::min(p.nc_lo, (lo_min + p.chunk_lo - 1) / p.chunk_lo);
   return p;
-}
-
-size_t workspace_bytes_for(const mikv_cache *c, const Plan &p) {
-  const int64_t BQ = (int64_t)c->batch * c->q_heads;
-  return (size_t)(BQ * (p.nc_hi + p.nc_lo) * kRec * 4 + BQ * c->cap_hi * 4);
 }
 
 AttnArgs make_args(const mikv_cache *c, const Plan &p, const uint16_t *q, const float *balance, float scale,

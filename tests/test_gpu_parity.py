@@ -415,6 +415,28 @@ def test_lockstep_gqa8():
         run.step(t)
 
 
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("shape", [
+    # importance pools that cross 64 and 96 tokens (chunks of 32) and retained
+    # pools that cross 1152 and 1024 (chunks of 128), at G = 4 and 8
+    dict(batch=1, q_heads=4, kv_heads=1, context=639),
+    dict(batch=1, q_heads=16, kv_heads=2, context=1278, hi_bits=8, group=64),
+    dict(batch=1, q_heads=8, kv_heads=1, context=958, hi_bits=4, group=32),
+    dict(batch=2, q_heads=8, kv_heads=2, context=1136, lo_bits=4, hi_bits=16),
+    # more heads: 48-token importance-pool chunks, 256-token retained ones
+    dict(batch=16, q_heads=32, kv_heads=8, context=2000, window=64),
+])
+def test_lockstep_short_chunks(shape, fused):
+    """Small GQA caches, whose chunks are shorter than 128 tokens."""
+    _dev()
+    wl = workloads.small_workload("mistral_7b", **{"window": 32, **shape})
+    steps = 2 if wl.batch > 4 else 4
+    run = Lockstep(wl, steps, fused=fused)
+    run.prefill()
+    for t in range(steps):
+        run.step(t)
+
+
 def test_lockstep_window_outside_ratio_many_demotions():
     """Budget shrinking faster than one token per step (window counted on top
     of a ratio that the workload then lowers) exercises the radix-select path
