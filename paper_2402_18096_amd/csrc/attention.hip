@@ -1562,10 +1562,9 @@ __device__ inline void merge_output(const AttnArgs &A, int qh0, int nc, const fl
 // two; the grids of many-head caches hold several blocks per CU.)
 template <int G>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G == 1 ? 8 : G == 2 ? 6 : 1)))
-void attn_finalize_kernel(AttnArgs A, int accumulate, int tiles_hi, int tiles_lo) {
+void attn_finalize_kernel(AttnArgs A, int accumulate, int tiles_hi, int tiles_lo, int per_query) {
   const int h = blockIdx.x, c = blockIdx.y;  // heads fastest: every head's block 0 is dispatched first
-  const int b = h / A.kv_heads, kvh = h % A.kv_heads;
-  const int qh0 = b * A.q_heads + kvh * G;
+  const int qh0 = h * G;  // = b * q_heads + kv head * G
   const int nc = A.nc_hi + A.nc_lo;
   float M[G], inv[G];
   if (c == 0) {  // the merge holds no tile
@@ -1576,7 +1575,12 @@ void attn_finalize_kernel(AttnArgs A, int accumulate, int tiles_hi, int tiles_lo
   const int tile = c - 1;
   const bool is_hi = tile < tiles_hi;
   const bool has_tile = is_hi || tile - tiles_hi < tiles_lo;
-  const ProbTile<G> T = prob_tile_load<G>(A, h, qh0, is_hi, is_hi ? tile : tile - tiles_hi, has_tile, accumulate);
+  // With a block per query head of a group the pool's size is the one that
+  // the partial phase noted in the record of its first chunk.
+  const int n_pool = per_query ? __builtin_bit_cast(int, A.partials[((int64_t)qh0 * nc + (is_hi ? 0 : A.nc_hi)) * kRec + kRecN])
+                               : -1;
+  const ProbTile<G> T =
+      prob_tile_load<G>(A, h, qh0, is_hi, is_hi ? tile : tile - tiles_hi, has_tile, accumulate, n_pool);
   head_stats<G>(A, qh0, nc, M, inv);
   if (has_tile) prob_tile_store<G>(A, h, qh0, is_hi, accumulate, T, M, inv);
 }
@@ -1991,8 +1995,8 @@ int decode_finalize_select(const mikv_cache *c, int32_t length, const uint16_t *
   const int tiles_hi = (span_hi + kProbTile - 1) / kProbTile;  // probabilities accumulated
   const int tiles_lo = A.probs_lo && !evicting(c) ? (span_lo + kProbTile - 1) / kProbTile : 0;
   const int kt = lo_tiles_per_block(group_size_of(c));
-  dim3 grid(n_heads_of(c), 2 + (tiles_lo + kt - 1) / kt);  // y = 0: importance pool and re-rank, 1: output
   const int G = group_size_of(c);
+  dim3 grid(n_heads_of(c), 2 + (tiles_lo + kt - 1) / kt);  // y = 0: importance pool and re-rank, 1: output
   switch (format_key(c)) {
     case 1602: launch_finalize_select<16, 2>(A, S, G, grid, tiles_hi, tiles_lo, st); break;
     case 1604: launch_finalize_select<16, 4>(A, S, G, grid, tiles_hi, tiles_lo, st); break;
@@ -2033,12 +2037,17 @@ int decode_finalize(const mikv_cache *c, int32_t length, const uint16_t *q, cons
   const int span_hi = std::min(length, c->cap_hi), span_lo = std::min(length, c->cap_lo);
   const int tiles_hi = (A.scores_hi && (A.probs_hi || A.acc)) ? (span_hi + kProbTile - 1) / kProbTile : 0;
   const int tiles_lo = A.probs_lo && !evicting(c) ? (span_lo + kProbTile - 1) / kProbTile : 0;
-  dim3 grid(n_heads_of(c), 1 + tiles_hi + tiles_lo);  // y = 0: output
-  switch (group_size_of(c)) {
-    case 1: hipLaunchKernelGGL(attn_finalize_kernel<1>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo); break;
-    case 2: hipLaunchKernelGGL(attn_finalize_kernel<2>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo); break;
-    case 4: hipLaunchKernelGGL(attn_finalize_kernel<4>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo); break;
-    default: hipLaunchKernelGGL(attn_finalize_kernel<8>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo); break;
+  // Without the importance update nothing is summed over the query heads of a
+  // KV head: each is a head of its own then, in G times the blocks of a G-th of
+  // the work (finalize of 4 x 64/8 x 7001 tokens 10.1 -> 5.3 us, of 16 x
+  // 64/8 x 8192 5 us less; MHA as before).
+  const int G = acc ? group_size_of(c) : 1, per_query = G != group_size_of(c);
+  dim3 grid(c->batch * c->q_heads / G, 1 + tiles_hi + tiles_lo);  // y = 0: output
+  switch (G) {
+    case 1: hipLaunchKernelGGL(attn_finalize_kernel<1>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo, per_query); break;
+    case 2: hipLaunchKernelGGL(attn_finalize_kernel<2>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo, per_query); break;
+    case 4: hipLaunchKernelGGL(attn_finalize_kernel<4>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo, per_query); break;
+    default: hipLaunchKernelGGL(attn_finalize_kernel<8>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo, per_query); break;
   }
   return check_launch("mikv_decode_attention_finalize");
 }
