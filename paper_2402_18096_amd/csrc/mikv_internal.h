@@ -167,28 +167,31 @@ __device__ inline void put_code(uint32_t w[BITS], int c, uint32_t v) {
   if (sh + BITS > 32) w[wi + 1] |= v >> (32 - sh);
 }
 
-// Integral fp32 codes t[32] of one lane's segment, already clamped, packed LSB
-// first into w[BITS].  Several codes are gathered in one fp32 number first
-// (fused multiply-adds, exact below 2^24), then converted at once.
-template <int BITS>
-__device__ inline void pack32(const float t[32], uint32_t w[BITS]) {
+// The 32 codes of one lane's segment, given by code(c) as integral fp32 numbers,
+// packed LSB first into w[BITS].  Several codes are gathered in one fp32 number
+// first (fused multiply-adds, exact below 2^24), then converted at once.  The
+// scheduling barriers keep one number's codes in registers instead of all 32.
+template <int BITS, class Code>
+__device__ inline void pack32(Code code, uint32_t w[BITS]) {
   if constexpr (BITS == 8) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       uint32_t v = 0u;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v = __builtin_amdgcn_cvt_pk_u8_f32(t[4 * i + e], e, v);
+      for (int e = 0; e < 4; ++e) v = __builtin_amdgcn_cvt_pk_u8_f32(code(4 * i + e), e, v);
       w[i] = v;
+      __builtin_amdgcn_sched_barrier(0);
     }
   } else {
     constexpr int N = BITS == 4 ? 4 : 8;  // codes per number: 16, 24 (3-bit) or 16 bits
     uint32_t part[32 / N];
 #pragma unroll
     for (int i = 0; i < 32 / N; ++i) {
-      float v = t[N * i + N - 1];
+      float v = code(N * i + N - 1);
 #pragma unroll
-      for (int e = N - 2; e >= 0; --e) v = fmaf(v, (float)(1 << BITS), t[N * i + e]);
+      for (int e = N - 2; e >= 0; --e) v = fmaf(v, (float)(1 << BITS), code(N * i + e));
       part[i] = (uint32_t)v;
+      __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (BITS == 3) {
       w[0] = part[0] | part[1] << 24;
@@ -209,7 +212,7 @@ __device__ inline void pack32(const float t[32], uint32_t w[BITS]) {
 // range clamp to the same code, so |Q| <= 2^BITS matters.  The rounded code can
 // differ only where a half-integer lies between the two, so where an
 // estimate is within 2^-20 (|beta r| + 2^BITS + 1) of a half-integer the wave
-// takes the true divide for its quotients; the codes are those of encode()
+// packs again from the true divide; the codes are those of encode()
 // bit for bit.  About seven VALU instructions per value, where a relative
 // test per value, a clamp, a conversion and a shift took some twenty.
 template <int BITS>
@@ -217,20 +220,18 @@ __device__ inline void encode32(const float x[32], const GroupParams &p, uint32_
   const float top = (float)((1 << BITS) - 1);
   const bool zero = p.a == 0.0f;
   const float ra = zero ? 0.0f : 1.0f / p.a, nb = -p.b * ra;
-  float t[32], far = 0.0f;  // far: the largest distance from the nearest integer
-#pragma unroll
-  for (int c = 0; c < 32; ++c) {
-    const float q = fmaf(x[c], ra, nb);
-    t[c] = rintf(q);
-    far = fmaxf(far, fabsf(q - t[c]));
-  }
+  float far = 0.0f;  // the largest distance from the nearest integer
+  pack32<BITS>(
+      [&](int c) {
+        const float q = fmaf(x[c], ra, nb), t = rintf(q);
+        far = fmaxf(far, fabsf(q - t));
+        return __builtin_amdgcn_fmed3f(t, 0.0f, top);
+      },
+      w);
   if (__ballot(!(far <= 0.5f - 0x1p-20f * (fabsf(nb) + (top + 2.0f))))) {
-#pragma unroll
-    for (int c = 0; c < 32; ++c) t[c] = zero ? 0.0f : rintf((x[c] - p.b) / p.a);
+    pack32<BITS>(
+        [&](int c) { return zero ? 0.0f : __builtin_amdgcn_fmed3f(rintf((x[c] - p.b) / p.a), 0.0f, top); }, w);
   }
-#pragma unroll
-  for (int c = 0; c < 32; ++c) t[c] = __builtin_amdgcn_fmed3f(t[c], 0.0f, top);
-  pack32<BITS>(t, w);
 }
 
 // Eq. 1 codes of the 32 channels [32 * lane4, 32 * lane4 + 32) of a key with

@@ -180,8 +180,13 @@ __device__ inline void load_hi_segment(const SelArgs &A, const uint8_t *rows, co
 }
 
 // Eq. 1 codes at LO_BITS of 32 decoded channels (a group spans group/32
-// lanes): the packed little-endian words and the group parameters.
-template <int LO_BITS>
+// lanes): the packed little-endian words and the group parameters.  TIGHT: one
+// divide per code instead of encode32, whose rare second pass over the divides
+// makes a kernel held to 96 registers spill (select_kernel, 1280 heads 10.0 ->
+// 11.4 us); in the fused finalize it shortens the re-rank's chain (256 heads
+// INT8 + INT4 10.3 -> 9.1 us per launch, 4 heads x 512 tokens 292 -> 277 us per
+// 16 steps and prompt).
+template <int LO_BITS, bool TIGHT>
 __device__ inline GroupParams lo_words(const SelArgs &A, const float x[32], uint32_t w[LO_BITS]) {
   float mn = x[0], mx = x[0];
 #pragma unroll
@@ -194,16 +199,20 @@ __device__ inline GroupParams lo_words(const SelArgs &A, const float x[32], uint
     mx = fmaxf(mx, __shfl_xor(mx, o, 64));
   }
   GroupParams p = group_params(mn, mx, LO_BITS);
+  if constexpr (TIGHT) {
 #pragma unroll
-  for (int i = 0; i < LO_BITS; ++i) w[i] = 0u;
+    for (int i = 0; i < LO_BITS; ++i) w[i] = 0u;
 #pragma unroll
-  for (int c = 0; c < 32; ++c) put_code<LO_BITS>(w, c, encode(x[c], p, LO_BITS));
+    for (int c = 0; c < 32; ++c) put_code<LO_BITS>(w, c, encode(x[c], p, LO_BITS));
+  } else {
+    encode32<LO_BITS>(x, p, w);
+  }
   return p;
 }
 
 // Eq. 1 at LO_BITS of 32 decoded channels into retained-pool slot lslot:
 // codes token-major, except 2-bit values of a GQA cache (tiled layout).
-template <int LO_BITS>
+template <int LO_BITS, bool TIGHT>
 __device__ inline void store_lo_segment(const SelArgs &A, int h, int64_t lslot, bool is_v, int part,
                                         const float x[32], int pos) {
   const int ng = kHeadDim / A.group;
@@ -217,7 +226,7 @@ __device__ inline void store_lo_segment(const SelArgs &A, int h, int64_t lslot, 
     for (int i = 0; i < LO_BITS; ++i) codes[i] = w[i];
     return;
   }
-  GroupParams p = lo_words<LO_BITS>(A, x, w);
+  GroupParams p = lo_words<LO_BITS, TIGHT>(A, x, w);
   if (LO_BITS == 2 && is_v && A.v_tiled) {
     store_int2_v(A.lo_v + (int64_t)h * A.cap_lo * (kHeadDim / 4), lslot - (int64_t)h * A.cap_lo, part, w);
   } else {
@@ -230,7 +239,7 @@ __device__ inline void store_lo_segment(const SelArgs &A, int h, int64_t lslot, 
     lane_pick(is_v, A.lo_vp, A.lo_kp)[lslot * ng + (part * 32) / A.group] = (uint32_t)p.a16 | ((uint32_t)p.b16 << 16);
 }
 
-template <int HI_BITS, int LO_BITS>
+template <int HI_BITS, int LO_BITS, bool TIGHT>
 __device__ inline void demote_row(const SelArgs &A, int h, int slot, int64_t lslot, int p) {
   if (threadIdx.x >= 8) return;
   const int ng = kHeadDim / A.group;
@@ -240,7 +249,7 @@ __device__ inline void demote_row(const SelArgs &A, int h, int slot, int64_t lsl
   const uint32_t *pars = HI_BITS == 16 ? nullptr : lane_pick(is_v, A.hi_vp, A.hi_kp) + (int64_t)h * A.cap_hi * ng;
   float x[32];
   load_hi_segment<HI_BITS>(A, rows, pars, slot, part, x);
-  store_lo_segment<LO_BITS>(A, h, lslot, is_v, part, x, p);
+  store_lo_segment<LO_BITS, TIGHT>(A, h, lslot, is_v, part, x, p);
   if (threadIdx.x == 0) {
     A.lo_pos[lslot] = p;
     if (A.map) A.map[(int64_t)h * A.max_len + p] = 0;
@@ -344,7 +353,7 @@ __device__ inline void select_scan(const SelArgs &A, int h, int from, int n, int
 // pool counts before the re-rank, `last` the prefetched last slot.  With
 // `set_n` (n_hi in memory does not yet count an appended token) n_hi is
 // written even when no token leaves.
-template <int HI_BITS, int LO_BITS>
+template <int HI_BITS, int LO_BITS, bool TIGHT = false>
 __device__ __attribute__((always_inline)) void select_finish(const SelArgs &A, int h, int n, int n_lo0, const SelScan &sc,
                               const SlotData<HI_BITS> &last, bool set_n = false) {
   __shared__ int s_tmp_i[kSel / 64];
@@ -375,7 +384,7 @@ __device__ __attribute__((always_inline)) void select_finish(const SelArgs &A, i
     const int slot = s_arg[0];
     // the key's low word is the position
     if (!A.evict)
-      demote_row<HI_BITS, LO_BITS>(A, h, slot, (int64_t)h * A.cap_lo + n_lo0, (int)(uint32_t)cut);
+      demote_row<HI_BITS, LO_BITS, TIGHT>(A, h, slot, (int64_t)h * A.cap_lo + n_lo0, (int)(uint32_t)cut);
     else if (threadIdx.x == 0 && A.map)
       A.map[(int64_t)h * A.max_len + (int)(uint32_t)cut] = 0;
     __syncthreads();
@@ -409,7 +418,7 @@ __device__ __attribute__((always_inline)) void select_finish(const SelArgs &A, i
     float x[32];
     load_hi_segment<HI_BITS>(A, rows, pars, slot, part, x);
     const int64_t lslot = (int64_t)h * A.cap_lo + n_lo0 + d;
-    store_lo_segment<LO_BITS>(A, h, lslot, is_v, part, x, pos[slot]);
+    store_lo_segment<LO_BITS, TIGHT>(A, h, lslot, is_v, part, x, pos[slot]);
     if (part == 0 && !is_v) {
       const int p = pos[slot];
       A.lo_pos[lslot] = p;
@@ -462,7 +471,7 @@ __device__ __attribute__((always_inline)) void select_head(const SelArgs &A, int
   // The last slot fills the hole of a demoted token: fetch it now, its
   // latency then hides behind the reductions.
   const SlotData<HI_BITS> last = n > 0 ? load_slot<HI_BITS>(A, h, n - 1) : SlotData<HI_BITS>{};
-  select_finish<HI_BITS, LO_BITS>(A, h, n, n_lo0, sc, last, A.pending != 0);
+  select_finish<HI_BITS, LO_BITS, true>(A, h, n, n_lo0, sc, last, A.pending != 0);
 }
 
 // Arguments of a select for the cache `c` (host side).
