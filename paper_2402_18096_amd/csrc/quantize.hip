@@ -205,7 +205,8 @@ __device__ inline int wave_count(const int32_t *counts, int n) {
 // Place tokens [chunk*kChunk, ...) of head blockIdx.y.  With `counts`
 // (mask given) slots come from the per-chunk counts and an in-block scan;
 // without, every token goes to the importance pool in order.  When `commit`
-// is set (a single chunk per head), the block also advances n_hi/n_lo.
+// is set (a single block per head), the block also advances n_hi/n_lo.  The
+// gridDim.z blocks of a chunk share out its rows; block 0 records the tokens.
 //
 // The rows are quantized pool by pool, keys then values, so that a wave runs
 // one format (a wave over neighbouring tokens nearly always held both pools,
@@ -220,6 +221,7 @@ __global__ __launch_bounds__(256) void place_kernel(Pools P, const uint16_t *k, 
                                                     const uint8_t *hi_mask, const float *score_init,
                                                     const int32_t *counts, int nchunks, int commit) {
   const int h = blockIdx.y, chunk = blockIdx.x, tid = threadIdx.x;
+  const int part = blockIdx.z, r0 = (tid >> 2) + part * (256 / 4), r_step = gridDim.z * (256 / 4);
   __shared__ int s_slot[kChunk];       // by order: retained-pool tokens first
   __shared__ uint8_t s_token[kChunk];  // order -> token of the chunk
   __shared__ int s_wave[kChunk / 64][2];
@@ -264,17 +266,19 @@ __global__ __launch_bounds__(256) void place_kernel(Pools P, const uint16_t *k, 
                ((pos0 + j) / kKeyBlock * kKeyBlock < pos0 || (pos0 + j) / kKeyBlock * kKeyBlock + kKeyBlock > pos0 + n)) {
       // a retained key needs its block's parameters: the block must lie
       // within the placed positions
-      atomicOr(P.status, MIKV_DEVERR_KEY_BLOCK);
+      if (part == 0) atomicOr(P.status, MIKV_DEVERR_KEY_BLOCK);
       slot = -1;
     } else if (slot >= cap) {
-      atomicOr(P.status, is_hi ? MIKV_DEVERR_HI_FULL : MIKV_DEVERR_LO_FULL);
+      if (part == 0) atomicOr(P.status, is_hi ? MIKV_DEVERR_HI_FULL : MIKV_DEVERR_LO_FULL);
       slot = -1;
     }
     const int o = is_hi ? cnt_lo + r_hi : r_lo;
     s_slot[o] = slot;
     s_token[o] = (uint8_t)tid;
     const int pos = pos0 + j;
-    if (slot >= 0) {
+    if (part != 0) {
+      // recorded by block 0
+    } else if (slot >= 0) {
       if (is_hi) {
         P.hi_pos[(int64_t)h * P.cap_hi + slot] = pos;
         P.hi_acc[(int64_t)h * P.cap_hi + slot] = score_init ? score_init[(int64_t)h * n + j] : 0.0f;
@@ -300,7 +304,7 @@ __global__ __launch_bounds__(256) void place_kernel(Pools P, const uint16_t *k, 
     const uint16_t *src = (is_v ? v : k) + ((int64_t)h * n + j0 + t) * kHeadDim + lane4 * 32;
     load_row_segment(src, !is_v && balance ? balance + (int64_t)h * kHeadDim + lane4 * 32 : nullptr, x);
   };
-  for (int r = tid >> 2; r < (P.evict ? 0 : 2 * cnt_lo); r += 256 / 4) {
+  for (int r = r0; r < (P.evict ? 0 : 2 * cnt_lo); r += r_step) {
     bool is_v;
     int t, slot;
     float x[32];
@@ -334,7 +338,7 @@ __global__ __launch_bounds__(256) void place_kernel(Pools P, const uint16_t *k, 
                                 store);
     }
   }
-  for (int r = tid >> 2; r < 2 * cnt_hi; r += 256 / 4) {
+  for (int r = r0; r < 2 * cnt_hi; r += r_step) {
     bool is_v;
     int t, slot;
     float x[32];
@@ -415,8 +419,14 @@ void launch_place(const mikv_cache *c, const uint16_t *k, const uint16_t *v, con
   if (hi_mask) {
     hipLaunchKernelGGL(count_hi_kernel, dim3(nchunks, NH), dim3(kChunk), 0, st, hi_mask, n, nchunks, counts);
   }
+  // a chunk's 512 rows take its block eight rounds of loads: where the chunks
+  // leave CUs idle (four blocks fit one), up to eight blocks share them (4
+  // heads x 512 tokens 19.5 -> 11.7 us); a single chunk keeps one block, which
+  // commits the counts itself
+  int parts = 1;
+  while (nchunks > 1 && parts < 8 && (int64_t)nchunks * NH * parts * 2 <= 1024) parts *= 2;
   int commit = nchunks == 1 ? 1 : 0;
-  hipLaunchKernelGGL((place_kernel<HI_BITS, LO_BITS>), dim3(nchunks, NH), dim3(256), 0, st, P, k, v, balance,
+  hipLaunchKernelGGL((place_kernel<HI_BITS, LO_BITS>), dim3(nchunks, NH, parts), dim3(256), 0, st, P, k, v, balance,
                      pos0, n, hi_mask, score_init, hi_mask ? counts : nullptr, nchunks, commit);
   if (!commit) {
     hipLaunchKernelGGL(commit_counts_kernel, dim3((NH + 3) / 4), dim3(256), 0, st, P, NH, n,
