@@ -234,6 +234,9 @@ extern "C" int mikv_select_prefill(const float *scores, int32_t n_heads, int32_t
   auto kernel = length <= 4 * kPre    ? select_prefill_kernel<4>
                 : length <= 16 * kPre ? select_prefill_kernel<16>
                                       : select_prefill_kernel<32>;
-  hipLaunchKernelGGL(kernel, dim3(n_heads), dim3(kPre), 0, (hipStream_t)stream, scores, length, k_heavy, window, hi_mask);
+  constexpr int kMost = 1 << 20;  // heads per launch: a grid's threads stay below 2^32
+  for (int64_t h0 = 0; h0 < n_heads; h0 += kMost)
+    hipLaunchKernelGGL(kernel, dim3((int)std::min<int64_t>(kMost, n_heads - h0)), dim3(kPre), 0, (hipStream_t)stream,
+                       scores + h0 * length, length, k_heavy, window, hi_mask + h0 * length);
   return check_launch("mikv_select_prefill");
 }
