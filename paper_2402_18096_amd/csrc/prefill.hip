@@ -57,7 +57,8 @@ __device__ inline int lds_word(int row, int c) { return row * kRowWords + (c ^ (
 // The streamed tile of TR rows goes from memory straight to LDS (each wave
 // instruction moves 1 KiB: four rows, lane l the word that belongs at word
 // l % 16 of row l / 16), through a descriptor that ends with the last row:
-// rows past it arrive as zeros.
+// rows past it arrive as zeros.  The whole offset is in the vector operand: the
+// scalar one is no part of the bounds check.
 template <int TR>
 __device__ inline void stage(u4_t *lds, const uint16_t *rows, int row0, int T) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -68,7 +69,7 @@ __device__ inline void stage(u4_t *lds, const uint16_t *rows, int row0, int T) {
 #pragma unroll
   for (int u = 0; u < TR / 16; ++u)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)(lds + (16 * u + 4 * wave) * kRowWords),
-                                             16, off, 16 * u * kHeadDim * 2, 0, 0);
+                                             16, off + 16 * u * kHeadDim * 2, 0, 0, 0);
 }
 
 __device__ inline void load_stationary(const uint16_t *base, int row0, int T, u4_t op[2][8]) {

@@ -587,6 +587,31 @@ def test_prefill_importance_tile_edges(B, Hq, Hkv, T, grow):
         np.testing.assert_allclose(got.reshape(NH, T)[h].cpu().numpy(), ref, rtol=1e-4, atol=1e-6, err_msg=f"head {h}")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv", [(1, 2, 2), (1, 8, 1), (2, 96, 96), (8, 96, 96)])
+@pytest.mark.parametrize("T", [1, 31, 33, 65, 129, 257])
+def test_prefill_importance_reads_no_row_past_the_prompt(B, Hq, Hkv, T):
+    """q and k as the leading part of larger buffers whose following rows are
+    NaN: the last tile of the last head must not see them (one, two and four
+    waves per 64 rows; same bound as above)."""
+    dev = _dev()
+    g = torch.Generator(device=dev)
+    g.manual_seed(T)
+
+    def rows(n):
+        buf = torch.full((n * T + 160, 128), float("nan"), dtype=torch.float16, device=dev)
+        buf[:n * T] = torch.randn(n * T, 128, generator=g, device=dev).half()
+        return buf[:n * T]
+
+    q, k = rows(B * Hq).view(B, Hq, T, 128), rows(B * Hkv).view(B, Hkv, T, 128)
+    got = torch.empty(B, Hkv, T, dtype=torch.float32, device=dev)
+    mikv.mikv_prefill_importance(q, k, got, SCALE)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(got).all())
+    ref = oracle.prefill_importance(np16(q.reshape(B * Hkv, Hq // Hkv, T, 128)[-1]), np16(k.reshape(-1, T, 128)[-1]),
+                                    SCALE)
+    np.testing.assert_allclose(got.reshape(-1, T)[-1].cpu().numpy(), ref, rtol=1e-4, atol=1e-6)
+
+
 def test_lockstep_with_prompt_importance():
     """A decode run whose first selection uses the prompt's own H2O scores
     (mikv_prefill_importance) instead of seeded ones: the oracle takes the
