@@ -58,18 +58,25 @@ __device__ inline int lds_word(int row, int c) { return row * kRowWords + (c ^ (
 // instruction moves 1 KiB: four rows, lane l the word that belongs at word
 // l % 16 of row l / 16), through a descriptor that ends with the last row:
 // rows past it arrive as zeros.  The whole offset is in the vector operand: the
-// scalar one is no part of the bounds check.
-template <int TR>
+// scalar one is no part of the bounds check.  REPEAT: past the prompt the last
+// row again instead (pass 2, whose sums take every query of the tile: such a
+// query's logit is infinite or NaN only where the last query's is, and its
+// statistics make it a probability of 0, where zeros would make NaN of an
+// infinite key; pass 1 masks the keys past its queries, where the clamp would
+// cost 0.3 %).
+template <int TR, bool REPEAT>
 __device__ inline void stage(u4_t *lds, const uint16_t *rows, int row0, int T) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int row = 4 * wave + (lane >> 4);
+  const int row = 4 * wave + (lane >> 4), last = min(TR, T - row0) - 1;
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t *>(rows + (int64_t)row0 * kHeadDim), (short)0, min(TR, T - row0) * kHeadDim * 2, 0x00020000);
-  const uint32_t off = 16u * (uint32_t)(row * kRowWords + ((lane & 15) ^ row));
+      const_cast<uint16_t *>(rows + (int64_t)row0 * kHeadDim), (short)0, (last + 1) * kHeadDim * 2, 0x00020000);
+  const uint32_t word = 16u * (uint32_t)((lane & 15) ^ row);
 #pragma unroll
-  for (int u = 0; u < TR / 16; ++u)
+  for (int u = 0; u < TR / 16; ++u) {
+    const int r = REPEAT ? min(row + 16 * u, last) : row + 16 * u;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)(lds + (16 * u + 4 * wave) * kRowWords),
-                                             16, off + 16 * u * kHeadDim * 2, 0, 0, 0);
+                                             16, (uint32_t)r * (kHeadDim * 2) + word, 0, 0, 0);
+  }
 }
 
 __device__ inline void load_stationary(const uint16_t *base, int row0, int T, u4_t op[2][8]) {
@@ -194,7 +201,7 @@ void prefill_rowstats_kernel(const uint16_t *q, const uint16_t *k, int q_heads, 
   const int i_base = (nblk - 1 - idx / G) * kCols;       // longest first
   const int i_wave = i_base + kWaveRows * wc;
   const uint16_t *qb = q + (int64_t)qh * T * kHeadDim, *kb = k + (int64_t)hk * T * kHeadDim;
-  stage<TR>(s_rows[0], kb, 0, T);
+  stage<TR, false>(s_rows[0], kb, 0, T);
   u4_t bq[2][8];
   load_stationary(qb, i_wave, T, bq);
   const uint32_t off = tile_offset();
@@ -245,7 +252,7 @@ void prefill_rowstats_kernel(const uint16_t *q, const uint16_t *k, int q_heads, 
       add(d1, 1, ts[0] + ts[1]);
       // after the tile's last LDS read: the compiler holds LDS reads back for
       // loads to LDS that are under way
-      if (s == 0) stage<TR>(s_rows[(t + 1) & 1], kb, min(t + 1, n_tiles - 1) * TR, T);
+      if (s == 0) stage<TR, false>(s_rows[(t + 1) & 1], kb, min(t + 1, n_tiles - 1) * TR, T);
       ts[0] = ts[1] = 0.0f;
       step<false>(d1, a[s], bq[1], d0, s2scale, m[0], a[0], rows, off, 0, use);
       add(d0, 0, ts[0] + ts[1]);
@@ -272,7 +279,7 @@ void prefill_rowstats_kernel(const uint16_t *q, const uint16_t *k, int q_heads, 
         add(d, cb, exp_sum(d, s2scale, m[cb]));
       }
     }
-    stage<TR>(s_rows[(t + 1) & 1], kb, min(t + 1, n_tiles - 1) * TR, T);
+    stage<TR, false>(s_rows[(t + 1) & 1], kb, min(t + 1, n_tiles - 1) * TR, T);
     wait_loads();
     __syncthreads();
   }
@@ -334,7 +341,7 @@ void prefill_colsum_kernel(const uint16_t *q, const uint16_t *k, int q_heads, in
   const int t_first = j_base / TR, t_end = (T + TR - 1) / TR, t_full = min(t_end, (j_base + kKeys - 1 + TR - 1) / TR);
   float2 ml = make_float2(0.0f, 0.0f);
   auto load = [&](int buf, int g, int t) {
-    stage<TR>(s_rows[buf], qb + (int64_t)g * T * kHeadDim, t * TR, T);
+    stage<TR, true>(s_rows[buf], qb + (int64_t)g * T * kHeadDim, t * TR, T);
     if (threadIdx.x < TR) {
       const int i = min(t * TR + (int)threadIdx.x, T - 1);
       ml = stb[(int64_t)g * T + i];

@@ -612,6 +612,28 @@ def test_prefill_importance_reads_no_row_past_the_prompt(B, Hq, Hkv, T):
     np.testing.assert_allclose(got.reshape(-1, T)[-1].cpu().numpy(), ref, rtol=1e-4, atol=1e-6)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv", [(1, 2, 2), (1, 8, 1), (2, 96, 96), (8, 96, 96)])
+@pytest.mark.parametrize("T", [5, 31, 33, 100, 257])
+def test_prefill_importance_masked_keys(B, Hq, Hkv, T):
+    """Keys that every query scores -inf (an infinite channel, as a mask
+    writes it) have probability 0: their scores are 0 and the others' those of
+    the oracle, also where the last tile is ragged."""
+    dev = _dev()
+    g = torch.Generator(device=dev)
+    g.manual_seed(T)
+    q, k = (torch.randn(B, h, T, 128, generator=g, device=dev).half() for h in (Hq, Hkv))
+    q[..., 0] = q[..., 0].abs() + 0.5
+    masked = sorted({1, T // 2, T - 1})
+    k[:, :, masked, 0] = -float("inf")
+    got = torch.empty(B, Hkv, T, dtype=torch.float32, device=dev)
+    mikv.mikv_prefill_importance(q, k, got, SCALE)
+    torch.cuda.synchronize()
+    assert bool((got[:, :, masked] == 0).all())
+    ref = oracle.prefill_importance(np16(q.reshape(B * Hkv, Hq // Hkv, T, 128)[-1]), np16(k.reshape(-1, T, 128)[-1]),
+                                    SCALE)
+    np.testing.assert_allclose(got.reshape(-1, T)[-1].cpu().numpy(), ref, rtol=1e-4, atol=1e-6)
+
+
 def test_lockstep_with_prompt_importance():
     """A decode run whose first selection uses the prompt's own H2O scores
     (mikv_prefill_importance) instead of seeded ones: the oracle takes the
