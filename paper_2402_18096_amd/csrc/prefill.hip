@@ -218,12 +218,12 @@ void prefill_rowstats_kernel(const uint16_t *q, const uint16_t *k, int q_heads, 
 #pragma unroll
         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, d[r]);
         const float mn = fmaxf(m[cb], mx * s2scale);
-        ts = 0.0f;
-        if (mn != -__builtin_huge_valf()) {
-          l[cb] *= m[cb] == -__builtin_huge_valf() ? 0.0f : __builtin_amdgcn_exp2f(m[cb] - mn);
-          m[cb] = mn;
-          ts = exp_sum(d, s2scale, mn);
-        }
+        // without a finite logit so far the sum is 0, or NaN (which the maximum
+        // passes over)
+        const float ref = mn == -__builtin_huge_valf() ? 0.0f : mn;
+        l[cb] *= m[cb] == -__builtin_huge_valf() ? 0.0f : __builtin_amdgcn_exp2f(m[cb] - ref);
+        m[cb] = mn;
+        ts = exp_sum(d, s2scale, ref);
       }
     }
     l[cb] += ts;
@@ -286,8 +286,9 @@ void prefill_rowstats_kernel(const uint16_t *q, const uint16_t *k, int q_heads, 
   // merge the two lanes of a query, then the WS waves
   auto merge = [](float &ma, float &la, float mb, float lb) {
     const float M = fmaxf(ma, mb);
-    la = (ma == -__builtin_huge_valf() ? 0.0f : la * __builtin_amdgcn_exp2f(ma - M)) +
-         (mb == -__builtin_huge_valf() ? 0.0f : lb * __builtin_amdgcn_exp2f(mb - M));
+    // (a side without a finite logit has the sum 0, or NaN)
+    la = (ma == -__builtin_huge_valf() ? la : la * __builtin_amdgcn_exp2f(ma - M)) +
+         (mb == -__builtin_huge_valf() ? lb : lb * __builtin_amdgcn_exp2f(mb - M));
     ma = M;
   };
 #pragma unroll

@@ -634,6 +634,26 @@ def test_prefill_importance_masked_keys(B, Hq, Hkv, T):
     np.testing.assert_allclose(got.reshape(-1, T)[-1].cpu().numpy(), ref, rtol=1e-4, atol=1e-6)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,bad", [
+    # every key of a lane's half of a tile, or of a wave's share of the tiles
+    (1, 2, 2, 8, slice(0, 4)), (1, 2, 2, 6, slice(0, 4)), (1, 4, 2, 100, slice(0, 32)), (2, 96, 96, 60, slice(0, 32)),
+    (8, 96, 96, 7, slice(0, 4)), (1, 2, 2, 100, slice(40, 41)), (1, 2, 2, 300, slice(0, 1)),
+])
+def test_prefill_importance_nan_keys_reach_every_later_query(B, Hq, Hkv, T, bad):
+    """A NaN key makes the whole probability row of every later query NaN, so
+    every score that such a query adds to (all of them: the last query attends
+    to every key)."""
+    dev = _dev()
+    g = torch.Generator(device=dev)
+    g.manual_seed(T)
+    q, k = (torch.randn(B, h, T, 128, generator=g, device=dev).half() for h in (Hq, Hkv))
+    k[:, :, bad] = float("nan")
+    got = torch.zeros(B, Hkv, T, dtype=torch.float32, device=dev)
+    mikv.mikv_prefill_importance(q, k, got, SCALE)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(got).all())
+
+
 def test_lockstep_with_prompt_importance():
     """A decode run whose first selection uses the prompt's own H2O scores
     (mikv_prefill_importance) instead of seeded ones: the oracle takes the
