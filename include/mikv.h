@@ -255,7 +255,10 @@ int mikv_quantize_kv(const mikv_cache *c, const uint16_t *k, const uint16_t *v, 
  *   flags     MIKV_ATTN_ACCUMULATE: also hi_acc[s] += sum over the group's
  *             query heads of probs_hi (left to right in head order, then one
  *             fp32 add) -- the importance update of this step, fused;
- *   workspace at least mikv_decode_workspace_size(c, length) bytes.
+ *   workspace at least mikv_decode_workspace_size(c, length) bytes.  The size
+ *             follows the split of that length, which grows coarser with the
+ *             cache, so it can shrink as length grows: one workspace for a
+ *             range of lengths takes the largest size of the range.
  * The call runs two phases that may also be launched separately:
  * _partial (per-chunk scores, softmax partials and value sums) and
  * _finalize (merge, probabilities, optional score update); both take the

@@ -1735,9 +1735,9 @@ size_t workspace_bytes_for(const mikv_cache *c, const Plan &p) {
 constexpr int64_t kFewWaves = 2048;
 constexpr size_t kFewWorkspace = (size_t)16 << 20;
 
-// size_bound: the plan with the most chunks the resident share can give
-// (workspaces are sized from it, so a workspace stays large enough when the
-// share changes).
+// size_bound: the plan with the most chunks the resident share can give, and
+// without the shorter chunks of few waves (workspace_need sizes workspaces
+// from it, so a workspace stays large enough when the share changes).
 Plan make_plan(const mikv_cache *c, int length, bool size_bound = false) {
   Plan p;
   const int64_t NH = n_heads_of(c);
@@ -1782,7 +1782,7 @@ Plan make_plan(const mikv_cache *c, int length, bool size_bound = false) {
   // 32/8 x 4096 19.3 -> 16.8; with one query head shorter chunks gain nothing
   // (1 x 40 x 5003: 15.2 -> 16.6).
   const int64_t base = NH * (p.nc_hi + p.nc_lo);
-  if (group_size_of(c) >= 4 && base < kFewWaves) {
+  if (!size_bound && group_size_of(c) >= 4 && base < kFewWaves) {
     const Plan wide = p;
     if (2 * base <= kFewWaves && p.nc_lo) p.chunk_lo = std::min(p.chunk_lo, 128);
     const int step = c->hi_bits == 4 ? 32 : 16;  // whole iterations
@@ -1798,6 +1798,23 @@ Plan make_plan(const mikv_cache *c, int length, bool size_bound = false) {
   const int lo_min = std::max(0, std::min(span_lo, length - c->cap_hi));
   p.nc_first = p.nc_hi + std::min(p.nc_lo, (lo_min + p.chunk_lo - 1) / p.chunk_lo);
   return p;
+}
+
+// Bytes of workspace for `length` tokens.  From four query heads per KV head
+// on a shorter length can have the more chunks (the shorter ones of few
+// waves), and a workspace made for a generation's last length serves all of
+// it: so the most records that such chunks can have at this or any shorter
+// length count (they are at least 32 and 128 tokens long and at most kFewWaves,
+// in at most kFewWorkspace bytes).
+size_t workspace_need(const mikv_cache *c, int length) {
+  const Plan p = make_plan(c, length, true);
+  const size_t need = workspace_bytes_for(c, p);
+  if (group_size_of(c) < 4) return need;
+  const int span_hi = std::min(length, c->cap_hi), span_lo = evicting(c) ? 0 : std::min(length, c->cap_lo);
+  Plan few = p;
+  few.nc_hi = (int)std::min<int64_t>(kFewWaves / n_heads_of(c), (span_hi + 31) / 32 + (span_lo + 127) / 128 + 1);
+  few.nc_lo = 0;
+  return std::max(need, std::min(workspace_bytes_for(c, few), kFewWorkspace));
 }
 
 AttnArgs make_args(const mikv_cache *c, const Plan &p, const uint16_t *q, const float *balance, float scale,
@@ -1915,7 +1932,7 @@ int check_attention_args(const mikv_cache *c, int32_t length, const uint16_t *q,
     return set_error(MIKV_ERR_INVALID_ARG, "%s: q and balance must be 16-byte aligned", who);
   if (length < 1) return set_error(MIKV_ERR_INVALID_ARG, "%s: length must be >= 1", who);
   if (length > c->max_len) return set_error(MIKV_ERR_CAPACITY, "%s: length %d > max_len %d", who, length, c->max_len);
-  size_t need = workspace_bytes_for(c, make_plan(c, length, true));
+  size_t need = workspace_need(c, length);
   if (!ws || ws_bytes < need) return set_error(MIKV_ERR_CAPACITY, "%s: workspace too small (%zu < %zu)", who, ws_bytes, need);
   return MIKV_OK;
 }
@@ -1928,7 +1945,7 @@ using namespace mikv;
 
 extern "C" size_t mikv_decode_workspace_size(const mikv_cache *c, int32_t length) {
   if (!c || length < 1 || validate_cache(c)) return 0;
-  return workspace_bytes_for(c, make_plan(c, length, true));
+  return workspace_need(c, length);
 }
 
 namespace mikv {

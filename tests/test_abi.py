@@ -234,6 +234,28 @@ def test_workspace_size_does_not_depend_on_the_resident_share(shape):
     assert sizes[0] == sizes[1] == sizes[2]
 
 
+@pytest.mark.parametrize("shape", [
+    dict(batch=4, q_heads=32, kv_heads=8, cap_hi=1766, max_len=8192),
+    dict(batch=1, q_heads=32, kv_heads=8, cap_hi=6681, max_len=32768),
+    dict(batch=1, q_heads=64, kv_heads=8, cap_hi=883, max_len=4096, hi_bits=8),
+    dict(batch=4, q_heads=64, kv_heads=8, cap_hi=1528, max_len=7008, hi_bits=8, group=64),
+    dict(batch=1, q_heads=32, kv_heads=4, cap_hi=6681, max_len=32768, lo_bits=4),
+    dict(batch=3, q_heads=16, kv_heads=4, cap_hi=2112, max_len=20480, hi_bits=4),
+    dict(batch=2, q_heads=64, kv_heads=8, cap_hi=2112, max_len=20480, lo_bits=0, cap_lo=0),
+])
+def test_workspace_of_the_last_length_serves_every_shorter_one(shape):
+    """A caller that sizes its workspace once, for a generation's last length,
+    is accepted at every length on the way, whatever chunks each one takes."""
+    L = mikv.lib()
+    c = _desc(**{"cap_lo": shape["max_len"], **shape})
+    c.hi_kp = c.hi_vp = 0x1000
+    most = 0
+    for length in range(1, c.max_len + 1, 13):
+        size = L.mikv_decode_workspace_size(ctypes.byref(c), length)
+        assert size >= most > 0 or most == 0 < size, length
+        most = size
+
+
 def test_resident_budget_fits_the_last_level_cache():
     """The attention's plainly-read share of a cache defaults to a positive
     size below the 256 MB last-level cache it is meant to stay in, and can be
