@@ -1561,24 +1561,41 @@ __device__ inline void merge_output(const AttnArgs &A, int qh0, int nc, const fl
   }
 }
 
-// Block (h, 0) merges the output of head h; blocks (h, 1..) turn one
-// probability tile each into probabilities (importance-pool tiles first).
-// Heads run along x, so the longest blocks, the merges, are dispatched first.
+// Output merge of one KV head by `merges` blocks, this one `block`: one block
+// for the group, or (merges = G) one per query head.
+template <int G>
+__device__ inline void merge_group(const AttnArgs &A, int qh0, int nc, int block, int merges) {
+  if constexpr (G >= 4) {
+    if (merges > 1) {
+      float M[1], inv[1];
+      head_stats<1>(A, qh0 + block, nc, M, inv);
+      merge_output<1>(A, qh0 + block, nc, M, inv);
+      return;
+    }
+  }
+  float M[G], inv[G];
+  head_stats<G>(A, qh0, nc, M, inv);
+  merge_output<G>(A, qh0, nc, M, inv);
+}
+
+// Blocks (h, 0 .. merges - 1) merge the output of head h; the blocks after
+// them turn one probability tile each into probabilities (importance-pool
+// tiles first).  Heads run along x, so the longest blocks, the merges, are
+// dispatched first.
 // (Register budget: 8 blocks per CU for one query head per KV head, 6 for
 // two; the grids of many-head caches hold several blocks per CU.)
 template <int G>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G == 1 ? 8 : G == 2 ? 6 : 1)))
-void attn_finalize_kernel(AttnArgs A, int accumulate, int tiles_hi, int tiles_lo, int per_query) {
-  const int h = blockIdx.x, c = blockIdx.y;  // heads fastest: every head's block 0 is dispatched first
+void attn_finalize_kernel(AttnArgs A, int accumulate, int tiles_hi, int tiles_lo, int per_query, int merges) {
+  const int h = blockIdx.x, c = blockIdx.y;  // heads fastest: every head's merges are dispatched first
   const int qh0 = h * G;  // = b * q_heads + kv head * G
   const int nc = A.nc_hi + A.nc_lo;
-  float M[G], inv[G];
-  if (c == 0) {  // the merge holds no tile
-    head_stats<G>(A, qh0, nc, M, inv);
-    merge_output<G>(A, qh0, nc, M, inv);
+  if (c < merges) {  // a merge holds no tile
+    merge_group<G>(A, qh0, nc, c, merges);
     return;
   }
-  const int tile = c - 1;
+  float M[G], inv[G];
+  const int tile = c - merges;
   const bool is_hi = tile < tiles_hi;
   const bool has_tile = is_hi || tile - tiles_hi < tiles_lo;
   // With a block per query head of a group the pool's size is the one that
@@ -1597,7 +1614,8 @@ void attn_finalize_kernel(AttnArgs A, int accumulate, int tiles_hi, int tiles_lo
 // the re-rank reads, runs the head's top-k and demotion on the scores it
 // still holds in registers (the positions and the last slot are loaded
 // with the tiles, so the re-rank adds one memory round trip: the demoted
-// row).  Block (h, 1) merges the output; blocks (h, 2..) handle the
+// row).  Blocks (h, 1 .. merges) merge the output: one block for the group, or
+// one per query head (merge_blocks); the blocks after them handle the
 // retained-pool tiles.  Heads run along x, so every head's re-rank block is
 // dispatched before any tile block.  No block waits on another.
 #ifndef MIKV_LO_TILES
@@ -1616,19 +1634,17 @@ __host__ __device__ constexpr int lo_tiles_per_block(int G) {
 }
 
 template <int G, int HI, int LO>
-__global__ __launch_bounds__(kBlock) void finalize_select_kernel(AttnArgs A, int tiles_hi, int tiles_lo, SelArgs S) {
+__global__ __launch_bounds__(kBlock) void finalize_select_kernel(AttnArgs A, int tiles_hi, int tiles_lo, int merges, SelArgs S) {
   static_assert(kSel == kBlock && kSelItems * kBlock == 2 * kProbTile, "select items = two probability tiles");
   const int h = blockIdx.x, c = blockIdx.y;  // heads fastest: every head's block 0 is dispatched first
   const int b = h / A.kv_heads, kvh = h % A.kv_heads;
   const int qh0 = b * A.q_heads + kvh * G;
   const int nc = A.nc_hi + A.nc_lo;
-  if (c == 1) {  // the merge holds no tile
-    float M[G], inv[G];
-    head_stats<G>(A, qh0, nc, M, inv);
-    merge_output<G>(A, qh0, nc, M, inv);
+  if (c >= 1 && c <= merges) {  // a merge holds no tile
+    merge_group<G>(A, qh0, nc, c - 1, merges);
     return;
   }
-  if (c > 1) {
+  if (c > merges) {
     // kLoTiles retained-pool tiles per block, all loaded before the
     // statistics: fewer, longer blocks (one round of blocks per step).
     // Block (h, 0) raises n_lo when it demotes, concurrently with this
@@ -1636,7 +1652,7 @@ __global__ __launch_bounds__(kBlock) void finalize_select_kernel(AttnArgs A, int
     // record of the head's first retained-pool chunk, written by the
     // partial phase.
     constexpr int KT = lo_tiles_per_block(G);
-    const int t0 = (c - 2) * KT;
+    const int t0 = (c - 1 - merges) * KT;
     const int n_lo_att = __builtin_bit_cast(
         int, A.partials[((int64_t)qh0 * nc + A.nc_hi) * kRec + kRecN]);
     ProbTile<G> T[KT];
@@ -1732,7 +1748,7 @@ size_t workspace_bytes_for(const mikv_cache *c, const Plan &p) {
   return (size_t)(BQ * (p.nc_hi + p.nc_lo) * kRec * 4 + BQ * c->cap_hi * 4);
 }
 
-constexpr int64_t kFewWaves = 2048;
+constexpr int64_t kSimds = 1024, kFewWaves = 2 * kSimds;
 constexpr size_t kFewWorkspace = (size_t)16 << 20;
 
 // size_bound: the plan with the most chunks the resident share can give, and
@@ -1773,31 +1789,61 @@ Plan make_plan(const mikv_cache *c, int length, bool size_bound = false) {
   chunks();
   // From four query heads per KV head on, a wave takes two (G = 8: four) times
   // as many iterations for an importance-pool chunk as for a retained-pool one,
-  // and while the waves all fit the chip at once (kFewWaves: two per SIMD) the
-  // longest of them is the launch.  Then shorter chunks: retained pool 128
-  // tokens while that many waves are free, importance pool down to 32 as long
-  // as the waves still fit.  Measured (us per attention, before -> after):
-  // 1 sequence x 64/8 heads x 4096 tokens 31.4 -> 19.3, 4 x 64/8 x 7001 50.1 ->
-  // 31.6 (36.8 in 16 % more waves than fit), 1 x 32/8 x 4096 17.2 -> 13.8, 4 x
-  // 32/8 x 4096 19.3 -> 16.8; with one query head shorter chunks gain nothing
-  // (1 x 40 x 5003: 15.2 -> 16.6).
+  // and while the waves all fit the chip at once the longest of them is the
+  // launch.  Then shorter chunks: retained pool 128 tokens while twice the
+  // waves still fit, importance pool down to 32 as long as they do.  What fits:
+  // at G = 8 two waves per SIMD; at G = 4, whose chunks are half as long, one
+  // while the long chunks leave SIMDs idle (two that share a SIMD take longer
+  // than the long chunk did: 2 x 32/8 heads x 8000 tokens, balanced fp16 + INT2,
+  // 18.9 us per attention in long chunks, 17.2 with one per SIMD, 19.6 with
+  // two; 14 x 32/8 x 710, INT8 + INT4, 18.3, 18.7, 24.2), and two when the long
+  // chunks already share them, where shorter ones even out the load (4 x 32/8 x
+  // 8192, INT8 + INT2, 23.0 -> 20.8), except for fp16 + INT2, where they only
+  // add records (2 x 32/8 x 12000 19.3 -> 20.2, balanced 20.5 -> 23.7).
+  // Measured (us per attention, long -> short): 1 sequence x 64/8 heads x 4096
+  // tokens 29.9 -> 16.0, 4 x 64/8 x 7001 46.1 -> 28.1, 1 x 32/8 x 4096 14.6 ->
+  // 11.4, 4 x 32/8 x 4096 17.1 -> 16.0; with one query head shorter chunks gain
+  // nothing (1 x 40 x 5003: 15.2 -> 16.6).  The whole step, whose merge reads
+  // the records (merge_blocks): 39.2 -> 26.1, 56.6 -> 38.3, 22.3 -> 18.9, 26.6
+  // -> 23.3; 1 x 32/4 x 32768 (464 records) 55.9 -> 51.4.
   const int64_t base = NH * (p.nc_hi + p.nc_lo);
-  if (!size_bound && group_size_of(c) >= 4 && base < kFewWaves) {
+  const int G = group_size_of(c);
+  const int64_t fit = G < 4 || base >= kFewWaves            ? 0
+                      : G >= 8                              ? kFewWaves
+                      : base < kSimds                       ? kSimds
+                      : c->hi_bits == 16 && c->lo_bits == 2 ? 0
+                                                            : kFewWaves;
+  if (!size_bound && fit) {
     const Plan wide = p;
-    if (2 * base <= kFewWaves && p.nc_lo) p.chunk_lo = std::min(p.chunk_lo, 128);
+    if (2 * base <= fit && p.nc_lo) p.chunk_lo = std::min(p.chunk_lo, 128);
     const int step = c->hi_bits == 4 ? 32 : 16;  // whole iterations
     for (p.chunk_hi = 32;; p.chunk_hi += step) {
       chunks();
-      if (p.chunk_hi >= wide.chunk_hi || NH * (p.nc_hi + p.nc_lo) <= kFewWaves) break;
+      if (p.chunk_hi >= wide.chunk_hi || NH * (p.nc_hi + p.nc_lo) <= fit) break;
     }
     // (a workspace that a caller's scratch of a fixed size held before still does)
-    if (NH * (p.nc_hi + p.nc_lo) > kFewWaves || workspace_bytes_for(c, p) > kFewWorkspace) p = wide;
+    if (NH * (p.nc_hi + p.nc_lo) > fit || workspace_bytes_for(c, p) > kFewWorkspace) p = wide;
   }
   // every token is in one of the pools, so at least length - cap_hi are in
   // the retained one (only the dispatch order depends on this)
   const int lo_min = std::max(0, std::min(span_lo, length - c->cap_hi));
   p.nc_first = p.nc_hi + std::min(p.nc_lo, (lo_min + p.chunk_lo - 1) / p.chunk_lo);
   return p;
+}
+
+// Blocks that merge the output of one KV head's group where the finalize
+// updates the importance (in both of its kernels, so that the decode step
+// and the separate calls agree bit for bit).  One block holds S = 8 / G splits of the records for each of the G
+// query heads, so at G = 8 it reads them all in turn, eight per round trip:
+// with the records of short chunks (or of few long-context heads) it outlasts
+// the rest of the launch (us per step, one block -> G: 1 x 32/4 heads x 32768
+// tokens, 464 records, 69.4 -> 51.6; 1 x 16/2 x 32768 65.2 -> 46.7; 23 x 32/8 x
+// 1113 36.1 -> 27.2).  A block per query head has eight splits.  With more waves
+// than fit the chip the merges of many heads share it and G blocks each read
+// the statistics for nothing: mistral_7b (5120 waves) 2 % slower.
+int merge_blocks(const mikv_cache *c, const Plan &p) {
+  const int G = group_size_of(c);
+  return G >= 4 && n_heads_of(c) * (int64_t)(p.nc_hi + p.nc_lo) <= kFewWaves ? G : 1;
 }
 
 // Bytes of workspace for `length` tokens.  From four query heads per KV head
@@ -1996,12 +2042,12 @@ int decode_partial(const mikv_cache *c, int32_t length, const uint16_t *q, const
 
 template <int HI, int LO>
 void launch_finalize_select(const AttnArgs &A, const SelArgs &S, int G, dim3 grid, int tiles_hi, int tiles_lo,
-                            hipStream_t st) {
+                            int merges, hipStream_t st) {
   switch (G) {
-    case 1: hipLaunchKernelGGL((finalize_select_kernel<1, HI, LO>), grid, dim3(kBlock), 0, st, A, tiles_hi, tiles_lo, S); break;
-    case 2: hipLaunchKernelGGL((finalize_select_kernel<2, HI, LO>), grid, dim3(kBlock), 0, st, A, tiles_hi, tiles_lo, S); break;
-    case 4: hipLaunchKernelGGL((finalize_select_kernel<4, HI, LO>), grid, dim3(kBlock), 0, st, A, tiles_hi, tiles_lo, S); break;
-    default: hipLaunchKernelGGL((finalize_select_kernel<8, HI, LO>), grid, dim3(kBlock), 0, st, A, tiles_hi, tiles_lo, S); break;
+    case 1: hipLaunchKernelGGL((finalize_select_kernel<1, HI, LO>), grid, dim3(kBlock), 0, st, A, tiles_hi, tiles_lo, merges, S); break;
+    case 2: hipLaunchKernelGGL((finalize_select_kernel<2, HI, LO>), grid, dim3(kBlock), 0, st, A, tiles_hi, tiles_lo, merges, S); break;
+    case 4: hipLaunchKernelGGL((finalize_select_kernel<4, HI, LO>), grid, dim3(kBlock), 0, st, A, tiles_hi, tiles_lo, merges, S); break;
+    default: hipLaunchKernelGGL((finalize_select_kernel<8, HI, LO>), grid, dim3(kBlock), 0, st, A, tiles_hi, tiles_lo, merges, S); break;
   }
 }
 
@@ -2019,17 +2065,19 @@ int decode_finalize_select(const mikv_cache *c, int32_t length, const uint16_t *
   const int tiles_lo = A.probs_lo && !evicting(c) ? (span_lo + kProbTile - 1) / kProbTile : 0;
   const int kt = lo_tiles_per_block(group_size_of(c));
   const int G = group_size_of(c);
-  dim3 grid(n_heads_of(c), 2 + (tiles_lo + kt - 1) / kt);  // y = 0: importance pool and re-rank, 1: output
+  const int merges = merge_blocks(c, p);
+  // y = 0: importance pool and re-rank, 1 .. merges: output
+  dim3 grid(n_heads_of(c), 1 + merges + (tiles_lo + kt - 1) / kt);
   switch (format_key(c)) {
-    case 1602: launch_finalize_select<16, 2>(A, S, G, grid, tiles_hi, tiles_lo, st); break;
-    case 1604: launch_finalize_select<16, 4>(A, S, G, grid, tiles_hi, tiles_lo, st); break;
-    case 1608: launch_finalize_select<16, 8>(A, S, G, grid, tiles_hi, tiles_lo, st); break;
-    case 802: launch_finalize_select<8, 2>(A, S, G, grid, tiles_hi, tiles_lo, st); break;
-    case 1603: launch_finalize_select<16, 3>(A, S, G, grid, tiles_hi, tiles_lo, st); break;
-    case 803: launch_finalize_select<8, 3>(A, S, G, grid, tiles_hi, tiles_lo, st); break;
-    case 402: launch_finalize_select<4, 2>(A, S, G, grid, tiles_hi, tiles_lo, st); break;
-    case 804: launch_finalize_select<8, 4>(A, S, G, grid, tiles_hi, tiles_lo, st); break;
-    default: launch_finalize_select<8, 8>(A, S, G, grid, tiles_hi, tiles_lo, st); break;
+    case 1602: launch_finalize_select<16, 2>(A, S, G, grid, tiles_hi, tiles_lo, merges, st); break;
+    case 1604: launch_finalize_select<16, 4>(A, S, G, grid, tiles_hi, tiles_lo, merges, st); break;
+    case 1608: launch_finalize_select<16, 8>(A, S, G, grid, tiles_hi, tiles_lo, merges, st); break;
+    case 802: launch_finalize_select<8, 2>(A, S, G, grid, tiles_hi, tiles_lo, merges, st); break;
+    case 1603: launch_finalize_select<16, 3>(A, S, G, grid, tiles_hi, tiles_lo, merges, st); break;
+    case 803: launch_finalize_select<8, 3>(A, S, G, grid, tiles_hi, tiles_lo, merges, st); break;
+    case 402: launch_finalize_select<4, 2>(A, S, G, grid, tiles_hi, tiles_lo, merges, st); break;
+    case 804: launch_finalize_select<8, 4>(A, S, G, grid, tiles_hi, tiles_lo, merges, st); break;
+    default: launch_finalize_select<8, 8>(A, S, G, grid, tiles_hi, tiles_lo, merges, st); break;
   }
   return check_launch("mikv_decode_step (finalize and select)");
 }
@@ -2065,12 +2113,13 @@ int decode_finalize(const mikv_cache *c, int32_t length, const uint16_t *q, cons
   // the work (finalize of 4 x 64/8 x 7001 tokens 10.1 -> 5.3 us, of 16 x
   // 64/8 x 8192 5 us less; MHA as before).
   const int G = acc ? group_size_of(c) : 1, per_query = G != group_size_of(c);
-  dim3 grid(c->batch * c->q_heads / G, 1 + tiles_hi + tiles_lo);  // y = 0: output
+  const int merges = per_query ? 1 : merge_blocks(c, p);
+  dim3 grid(c->batch * c->q_heads / G, merges + tiles_hi + tiles_lo);  // y < merges: output
   switch (G) {
-    case 1: hipLaunchKernelGGL(attn_finalize_kernel<1>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo, per_query); break;
-    case 2: hipLaunchKernelGGL(attn_finalize_kernel<2>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo, per_query); break;
-    case 4: hipLaunchKernelGGL(attn_finalize_kernel<4>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo, per_query); break;
-    default: hipLaunchKernelGGL(attn_finalize_kernel<8>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo, per_query); break;
+    case 1: hipLaunchKernelGGL(attn_finalize_kernel<1>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo, per_query, merges); break;
+    case 2: hipLaunchKernelGGL(attn_finalize_kernel<2>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo, per_query, merges); break;
+    case 4: hipLaunchKernelGGL(attn_finalize_kernel<4>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo, per_query, merges); break;
+    default: hipLaunchKernelGGL(attn_finalize_kernel<8>, grid, dim3(kBlock), 0, st, A, acc, tiles_hi, tiles_lo, per_query, merges); break;
   }
   return check_launch("mikv_decode_attention_finalize");
 }

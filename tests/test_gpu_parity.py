@@ -423,8 +423,15 @@ def test_lockstep_gqa8():
     dict(batch=1, q_heads=16, kv_heads=2, context=1278, hi_bits=8, group=64),
     dict(batch=1, q_heads=8, kv_heads=1, context=958, hi_bits=4, group=32),
     dict(batch=2, q_heads=8, kv_heads=2, context=1136, lo_bits=4, hi_bits=16),
-    # more heads: 48-token importance-pool chunks, 256-token retained ones
+    # more heads, 256-token retained chunks: 48-token importance-pool ones in one
+    # wave per SIMD, then (INT8) in two; whole ones for fp16 + INT2 there
+    dict(batch=8, q_heads=32, kv_heads=8, context=2000, window=64),
+    dict(batch=16, q_heads=32, kv_heads=8, context=2000, window=64, hi_bits=8),
     dict(batch=16, q_heads=32, kv_heads=8, context=2000, window=64),
+    # some 180 records per head: several rounds of the output merge, which the
+    # fused step does in a block per query head
+    dict(batch=1, q_heads=8, kv_heads=1, context=16001),
+    dict(batch=1, q_heads=8, kv_heads=2, context=16001, lo_bits=4),
 ])
 def test_lockstep_short_chunks(shape, fused):
     """Small GQA caches, whose chunks are shorter than 128 tokens."""
