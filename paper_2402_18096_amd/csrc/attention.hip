@@ -1265,12 +1265,12 @@ constexpr int unroll_for() {
 #endif
 template <int HI, int G>
 constexpr int unroll_hi() { return HI == 16 && G == 1 ? MIKV_UNROLL_F16_MHA : unroll_for<HI>(); }
-// An INT4 retained pool with one query head per KV head and no balancer takes
-// two tiles instead of four: fewer registers, one wave more per SIMD
-// (llama2_7b, 64 steps and prompt 2905 -> 2868 us; 1 x 32 heads x 4096 13.06 ->
-// 12.84 us per attention; an INT3 pool is 2 % slower with two).
-template <int LO, int G, bool SPLITQ>
-constexpr int unroll_lo() { return LO == 4 && G == 1 && !SPLITQ ? 2 : unroll_for<LO, SPLITQ>(); }
+// LEAN: an INT4 retained pool with one query head per KV head and no balancer
+// takes two tiles instead of four: fewer registers, one wave more per SIMD,
+// which rows from the last-level cache want (partial_lean); an INT3 pool is
+// 2 % slower with two.
+template <int LO, bool SPLITQ, bool LEAN>
+constexpr int unroll_lo() { return LEAN ? 2 : unroll_for<LO, SPLITQ>(); }
 template <int BITS>
 constexpr int prefetch_for() { return BITS <= 4 ? MIKV_PREFETCH_LOWBIT : MIKV_PREFETCH_HIGHBIT; }
 
@@ -1316,7 +1316,7 @@ __device__ inline void append_in_chunk(const AttnArgs &A, int h, int chunk) {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-template <int HI, int LO, int G, bool SPLITQ, bool KPC = false>
+template <int HI, int LO, int G, bool SPLITQ, bool KPC = false, bool LEAN = false>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MIKV_WAVES_PER_EU)))
 void attn_partial_kernel(AttnArgs A) {
   constexpr int CPL = G >= MIKV_NARROW_FROM_G ? 16 : 32;  // channels per lane
@@ -1393,9 +1393,9 @@ void attn_partial_kernel(AttnArgs A) {
     }
   } else {
     if (h < A.res_lo)
-      attn_chunk<LO, G, CPL_LO, SPLITQ, unroll_lo<LO, G, SPLITQ>(), prefetch_for<LO>()>(A, h, c - A.nc_hi, c, false, s_lds);
+      attn_chunk<LO, G, CPL_LO, SPLITQ, unroll_lo<LO, SPLITQ, LEAN>(), prefetch_for<LO>()>(A, h, c - A.nc_hi, c, false, s_lds);
     else
-      attn_chunk<LO, G, CPL_LO, SPLITQ, unroll_lo<LO, G, SPLITQ>(), prefetch_for<LO>(), false, true>(A, h, c - A.nc_hi, c, false, s_lds);
+      attn_chunk<LO, G, CPL_LO, SPLITQ, unroll_lo<LO, SPLITQ, LEAN>(), prefetch_for<LO>(), false, true>(A, h, c - A.nc_hi, c, false, s_lds);
   }
 }
 
@@ -1949,8 +1949,24 @@ void set_append(AttnArgs &A, const mikv_cache *c, int32_t length, const uint16_t
   A.hi_pending = 1;
 }
 
+// Whether an INT4 retained pool takes its rows two tiles at a time (unroll_lo):
+// while at least half of the cache is read from the last-level cache.  Measured
+// (us per attention, four tiles -> two): 8 x 32 heads x 4096 tokens, INT8 + INT4,
+// 229 MB 38.2 -> 36.9; 16 x 32 x 2000 40.8 -> 39.4; 2 x 32 x 32768, 397 MB 69.0 ->
+// 68.1; but mostly streamed, where bytes in flight count, 16 x 32 x 8192, fp16 +
+// INT4, 905 MB 139.5 -> 142.3; 32 x 40 x 8192, INT8 + INT4, 2.3 GB 364 -> 375.
+bool partial_lean(const mikv_cache *c, const Plan &p) {
+  return n_heads_of(c) * (p.head_bytes_hi + p.head_bytes_lo) <= 2 * resident_budget();
+}
+
 template <int HI, int LO, bool SPLITQ>
-void launch_partial_q(const AttnArgs &A, int G, dim3 grid, hipStream_t st) {
+void launch_partial_q(const AttnArgs &A, int G, bool lean, dim3 grid, hipStream_t st) {
+  if constexpr (LO == 4 && !SPLITQ) {
+    if (G == 1 && lean) {
+      hipLaunchKernelGGL((attn_partial_kernel<HI, LO, 1, SPLITQ, false, true>), grid, dim3(64), 0, st, A);
+      return;
+    }
+  }
   switch (G) {
     case 1: hipLaunchKernelGGL((attn_partial_kernel<HI, LO, 1, SPLITQ>), grid, dim3(64), 0, st, A); break;
     case 2: hipLaunchKernelGGL((attn_partial_kernel<HI, LO, 2, SPLITQ>), grid, dim3(64), 0, st, A); break;
@@ -1962,11 +1978,11 @@ void launch_partial_q(const AttnArgs &A, int G, dim3 grid, hipStream_t st) {
 // A balanced query (q / b) is not an fp16 value in general: carry it as two
 // fp16 parts.  An unbalanced query is fp16 already.
 template <int HI, int LO>
-void launch_partial_g(const AttnArgs &A, int G, dim3 grid, hipStream_t st) {
+void launch_partial_g(const AttnArgs &A, int G, bool lean, dim3 grid, hipStream_t st) {
   if (A.balance)
-    launch_partial_q<HI, LO, true>(A, G, grid, st);
+    launch_partial_q<HI, LO, true>(A, G, lean, grid, st);
   else
-    launch_partial_q<HI, LO, false>(A, G, grid, st);
+    launch_partial_q<HI, LO, false>(A, G, lean, grid, st);
 }
 
 int check_attention_args(const mikv_cache *c, int32_t length, const uint16_t *q, const float *balance, float *out,
@@ -2015,6 +2031,7 @@ int decode_partial(const mikv_cache *c, int32_t length, const uint16_t *q, const
   if (length & 1) A.order = c->hi_bits == 16 && group_size_of(c) == 1 ? 2 : 1;
   dim3 grid((p.nc_hi + p.nc_lo) * n_heads_of(c));
   const int G = group_size_of(c);
+  const bool lean = partial_lean(c, p);
   if (c->key_block) {
     // per-channel retained keys: fp16 importance pool, one query head per
     // KV head, no balancer (validated)
@@ -2027,15 +2044,15 @@ int decode_partial(const mikv_cache *c, int32_t length, const uint16_t *q, const
     return check_launch("mikv_decode_attention_partial");
   }
   switch (format_key(c)) {
-    case 1602: launch_partial_g<16, 2>(A, G, grid, st); break;
-    case 1604: launch_partial_g<16, 4>(A, G, grid, st); break;
-    case 1608: launch_partial_g<16, 8>(A, G, grid, st); break;
-    case 802: launch_partial_g<8, 2>(A, G, grid, st); break;
-    case 1603: launch_partial_g<16, 3>(A, G, grid, st); break;
-    case 803: launch_partial_g<8, 3>(A, G, grid, st); break;
-    case 402: launch_partial_g<4, 2>(A, G, grid, st); break;
-    case 804: launch_partial_g<8, 4>(A, G, grid, st); break;
-    default: launch_partial_g<8, 8>(A, G, grid, st); break;
+    case 1602: launch_partial_g<16, 2>(A, G, lean, grid, st); break;
+    case 1604: launch_partial_g<16, 4>(A, G, lean, grid, st); break;
+    case 1608: launch_partial_g<16, 8>(A, G, lean, grid, st); break;
+    case 802: launch_partial_g<8, 2>(A, G, lean, grid, st); break;
+    case 1603: launch_partial_g<16, 3>(A, G, lean, grid, st); break;
+    case 803: launch_partial_g<8, 3>(A, G, lean, grid, st); break;
+    case 402: launch_partial_g<4, 2>(A, G, lean, grid, st); break;
+    case 804: launch_partial_g<8, 4>(A, G, lean, grid, st); break;
+    default: launch_partial_g<8, 8>(A, G, lean, grid, st); break;
   }
   return check_launch("mikv_decode_attention_partial");
 }
