@@ -18,6 +18,7 @@
 // so a lane holds one query per tile: its statistics are two scalars, and a
 // logit costs one FMA, one exp2 and one add (pass 1) or FMA (pass 2).
 // Tiles entirely below the causal diagonal (nearly all) skip the mask.
+// Short prompts have a kernel of their own for each pass (short_pass).
 // Bound: the matrix cores and the VALU together, at the clock the chip holds
 // under both (about 2 GHz): per 32 x 32 tile 256 cycles of MFMA beside some 300
 // of FMA, exp2 and add.  Streaming through LDS instead of by every wave from
@@ -29,6 +30,8 @@
 // Lane l of a wave: operand row l % 32, channels [16 i + 8 (l / 32), + 8) of
 // MFMA i (the same split on both sides, so eight MFMAs cover 128 channels);
 // result register r is tile row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.
+#include <algorithm>
+
 #include "mikv_internal.h"
 
 namespace mikv {
@@ -444,27 +447,224 @@ void prefill_colsum_kernel(const uint16_t *q, const uint16_t *k, int q_heads, in
   if (kj < T) scores[(int64_t)hk * T + kj] = v;
 }
 
-// Launch of one pass: WS, the grid and the length of a run.
+// The passes of short prompts: one wave per 64 stationary rows, the streamed
+// rows straight from memory, 16 at a time, through v_mfma_f32_16x16x32_f16.
+// Bound: latency (a wave's chain is at most a few tiles); so 64-thread blocks without
+// LDS, many to a CU, instead of two blocks of four waves that fill a 128-row
+// tile first (short_pass has both sides' times).  Lane 16 a + n: operand row n
+// of a tile, channels [32 c + 8 a, + 8) of MFMA c; result registers r are
+// rows (queries) 4 a + r, column (key) n.
+constexpr int kShortTiles = 4;  // 16-row tiles per wave (64 rows)
+constexpr int kGridHeads = 65535;  // heads along the grid's y (its limit), the rest along z; a head's blocks follow each other
+constexpr float kLazy = 8.0f;   // raise a query's running maximum only past this (log2 units)
+
+typedef float f4_t __attribute__((ext_vector_type(4)));
+
+// Operands of row `row` of a [T, 128] fp16 matrix (zero past T).
+__device__ inline void load_rows16(const uint16_t *base, int row, int T, int a, u4_t op[4]) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    op[c] = row < T ? *reinterpret_cast<const u4_t *>(base + (int64_t)row * kHeadDim + 32 * c + 8 * a) : u4_t{0, 0, 0, 0};
+}
+
+__device__ inline f4_t logits16(const u4_t query[4], const u4_t key[4]) {
+  f4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) d = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_h8(query[c]), as_h8(key[c]), d, 0, 0, 0);
+  return d;
+}
+
+// Reductions over the 16 lanes of one logit row.
+__device__ inline float max16(float v) {
+  v = fmaxf(v, dpp_mov<0xB1>(v));
+  v = fmaxf(v, dpp_mov<0x4E>(v));
+  v = fmaxf(v, dpp_mov<0x141>(v));
+  return fmaxf(v, dpp_mov<0x140>(v));
+}
+__device__ inline float sum16(float v) {
+  v += dpp_mov<0xB1>(v);
+  v += dpp_mov<0x4E>(v);
+  v += dpp_mov<0x141>(v);
+  return v + dpp_mov<0x140>(v);
+}
+
+// Pass 1, block = 64 queries of one query head.
+__global__ __launch_bounds__(64) void short_rowstats_kernel(const uint16_t *q, const uint16_t *k, int q_heads,
+                                                            int kv_heads, int heads, int T, float s2scale, float2 *stats) {
+  const int lane = threadIdx.x, n = lane & 15, a = lane >> 4;
+  const int qh = blockIdx.z * kGridHeads + blockIdx.y, i_base = blockIdx.x * 16 * kShortTiles;
+  if (qh >= heads) return;
+  const int hk = qh / (q_heads / kv_heads);
+  const uint16_t *qb = q + (int64_t)qh * T * kHeadDim, *kb = k + (int64_t)hk * T * kHeadDim;
+  u4_t aq[kShortTiles][4];
+#pragma unroll
+  for (int rb = 0; rb < kShortTiles; ++rb) load_rows16(qb, i_base + 16 * rb + n, T, a, aq[rb]);
+  // The maximum is the same in the 16 lanes of a row and raised only when a
+  // logit exceeds it by more than kLazy, decided for the whole wave with one
+  // ballot; each lane sums its own terms.
+  float m[kShortTiles][4], l[kShortTiles][4];
+#pragma unroll
+  for (int rb = 0; rb < kShortTiles; ++rb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      m[rb][r] = -__builtin_huge_valf();
+      l[rb][r] = 0.0f;
+    }
+  const int j_end = min(T, i_base + 16 * kShortTiles);  // keys past the last query are masked
+  for (int j0 = 0; j0 < j_end; j0 += 16) {
+    u4_t bk[4];
+    load_rows16(kb, j0 + n, T, a, bk);
+    const int kj = j0 + n;
+#pragma unroll
+    for (int rb = 0; rb < kShortTiles; ++rb) {
+      if (j0 > i_base + 16 * rb + 15) continue;  // above the diagonal (wave-uniform)
+      const f4_t d = logits16(aq[rb], bk);
+      // a tile below the diagonal and inside the prompt needs no mask
+      const bool full = j0 + 15 <= i_base + 16 * rb && i_base + 16 * rb + 15 < T;  // wave-uniform
+      float s[4];
+      bool raise = false;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int qi = i_base + 16 * rb + 4 * a + r;
+        s[r] = full || (kj <= qi && qi < T) ? d[r] * s2scale : -__builtin_huge_valf();
+        raise = raise || s[r] > m[rb][r] + kLazy;
+      }
+      if (__ballot(raise)) {  // wave-uniform
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float mn = fmaxf(m[rb][r], max16(s[r]));
+          if (mn != m[rb][r]) {  // row-uniform; mn is finite here
+            l[rb][r] *= m[rb][r] == -__builtin_huge_valf() ? 0.0f : __builtin_amdgcn_exp2f(m[rb][r] - mn);
+            m[rb][r] = mn;
+          }
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) l[rb][r] += s[r] == -__builtin_huge_valf() ? 0.0f : __builtin_amdgcn_exp2f(s[r] - m[rb][r]);
+    }
+  }
+#pragma unroll
+  for (int rb = 0; rb < kShortTiles; ++rb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float sum = sum16(l[rb][r]);
+      const int qi = i_base + 16 * rb + 4 * a + r;
+      if (n == 0 && qi < T) stats[(int64_t)qh * T + qi] = make_float2(m[rb][r], 1.0f / sum);
+    }
+}
+
+// Pass 2, block = 64 keys of one KV head.
+__global__ __launch_bounds__(64) void short_colsum_kernel(const uint16_t *q, const uint16_t *k, int q_heads, int kv_heads,
+                                                          int heads, int T, float s2scale, const float2 *stats,
+                                                          float *scores) {
+  const int lane = threadIdx.x, n = lane & 15, a = lane >> 4;
+  const int hk = blockIdx.z * kGridHeads + blockIdx.y, j_base = blockIdx.x * 16 * kShortTiles;
+  if (hk >= heads) return;
+  const int G = q_heads / kv_heads;
+  const uint16_t *kb = k + (int64_t)hk * T * kHeadDim;
+  u4_t bk[kShortTiles][4];
+#pragma unroll
+  for (int cb = 0; cb < kShortTiles; ++cb) load_rows16(kb, j_base + 16 * cb + n, T, a, bk[cb]);
+  float cs[kShortTiles];
+#pragma unroll
+  for (int cb = 0; cb < kShortTiles; ++cb) cs[cb] = 0.0f;
+  for (int g = 0; g < G; ++g) {
+    const int qh = hk * G + g;  // = b * q_heads + head
+    const uint16_t *qb = q + (int64_t)qh * T * kHeadDim;
+    const float2 *st = stats + (int64_t)qh * T;
+    for (int i0 = j_base; i0 < T; i0 += 16) {
+      u4_t aq[4];
+      load_rows16(qb, i0 + n, T, a, aq);
+      float2 ml[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int qi = i0 + 4 * a + r;
+        ml[r] = qi < T ? st[qi] : make_float2(0.0f, 0.0f);
+      }
+#pragma unroll
+      for (int cb = 0; cb < kShortTiles; ++cb) {
+        if (j_base + 16 * cb > i0 + 15) continue;  // above the diagonal (wave-uniform)
+        const f4_t d = logits16(aq, bk[cb]);
+        const int kj = j_base + 16 * cb + n;
+        const bool full = j_base + 16 * cb + 15 <= i0 && i0 + 15 < T;  // no mask (wave-uniform)
+        if (full) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            cs[cb] = fmaf(__builtin_amdgcn_exp2f(fmaf(d[r], s2scale, -ml[r].x)), ml[r].y, cs[cb]);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int qi = i0 + 4 * a + r;
+            const bool valid = kj <= qi && qi < T;
+            const float p = __builtin_amdgcn_exp2f(fmaf(d[r], s2scale, -ml[r].x)) * ml[r].y;
+            cs[cb] += valid ? p : 0.0f;
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int cb = 0; cb < kShortTiles; ++cb) {
+    float v = cs[cb] + __shfl_xor(cs[cb], 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    const int kj = j_base + 16 * cb + n;
+    if (a == 0 && kj < T) scores[(int64_t)hk * T + kj] = v;
+  }
+}
+
+// Launch of one pass: WS (0: a short prompt's kernel), the blocks of a head and
+// the length of a run.
 struct Grid {
   int ws, nblk, run;
   dim3 blocks;
 };
 
+// Whether a pass (its stationary rows in `heads` heads, G the query heads it
+// streams per block in pass 2, 0 in pass 1) takes the short kernel.  Per block of
+// 64 rows that one does about half the work per time once the tiles are
+// full, but its blocks take neither LDS nor a whole 128-row tile, and some
+// eight times as many fit the chip.  Pass 1 (few rows to stream): a handful of
+// tokens, up to 112 as the heads fill the chip several times, and up to 192 where
+// blocks of 128 and 256 rows would be mostly padding.  Pass 2, which ends
+// in a reduction over 32 columns and four waves, up to 192 tokens in all over
+// the streamed heads or with many heads, and just past 256 likewise.  Measured
+// (both passes, us, the long kernels -> this): 1 x 4/4 heads x 1 token 14.5 ->
+// 7.0, 1 x 32/8 x 33 20.3 -> 15, 32 x 40 x 64 48 -> 20, 512 x 32 x 100 688 -> 398,
+// 512 x 32 x 300 2273 -> 1540, 1 x 64/8 x 100 26.8 against 50.8.
+bool short_pass(int heads, int G, int T) {
+  if (G == 0) return T <= std::min(112, 16 + heads / 16) || (heads >= 2048 && T > 128 && T <= std::min(192, 128 + heads / 64));
+  return T <= (heads >= 1024 ? 192 : 32 + 160 / G) || (heads >= (G == 1 ? 512 : 1024) && T > 256 && T <= 320 + 64 / G);
+}
+
 // `heads` heads of T stationary rows in `units` units of the same streamed
 // rows.  WS = 1 streams each row past 256 stationary ones, WS = 2 and 4 past 128
 // and 64, in two and four times as many blocks of a half and a quarter of the
 // work: better only while the grid leaves CUs idle (two blocks fit a CU, so
-// 512 fill the chip).  Measured (us for both passes, WS = 1 / 2 / 4, by the
+// 512 fill the chip; pass 2 in one round of equal blocks, T <= 256, stays with
+// WS = 1: 512 x 4/4 x 160 93 against 100 us) or where 256 rows are mostly
+// padding.  Measured (us for both passes, WS = 1 / 2 / 4, by the
 // blocks of WS = 1): 4096 blocks 1511 / 1557 / 1954, 1024: 347 / 365 / 440,
 // 256: 701 / 648 / 695, 240: 77 / 57 / 66, 64: 36 / 27 / 22.
 // Runs of 32 read less from beyond L2 than runs of 4 (4096 blocks: 1380
 // against 1481 us, 32768: 35.2 against 36.7 ms), but leave a longer tail,
 // which decides while the grid is only a few rounds (1024 blocks: 410 against
 // 336 us).
-Grid plan_grid(int heads, int units, int T) {
-  const int64_t n1 = (int64_t)heads * ((T + 255) / 256);
+Grid plan_pass(int heads, int units, int G, int T) {
   Grid g;
-  g.ws = n1 >= 768 ? 1 : n1 >= 192 ? 2 : 4;
+  if (short_pass(heads, G, T)) {
+    g.ws = 0;
+    g.run = 1;
+    g.nblk = (T + 16 * kShortTiles - 1) / (16 * kShortTiles);
+    g.blocks = dim3(g.nblk, std::min(heads, kGridHeads), (heads + kGridHeads - 1) / kGridHeads);
+    return g;
+  }
+  const int64_t n1 = (int64_t)heads * ((T + 255) / 256);
+  g.ws = n1 >= (G && T <= 256 ? 512 : 768) ? 1 : n1 >= 192 ? 2 : 4;
+  const bool half_empty = T % 256 != 0 && T % 256 <= 128;  // of the last 256 rows
+  if (T <= 64)
+    g.ws = 4;
+  else if (g.ws == 1 && half_empty && T < (G ? 320 : 512))
+    g.ws = 2;
   const int cols = kWaveRows * 4 / g.ws;
   g.nblk = (T + cols - 1) / cols;
   const int per_unit = g.nblk * (heads / units);
@@ -505,12 +705,22 @@ extern "C" int mikv_prefill_importance(const uint16_t *q_prefill, const uint16_t
   hipStream_t st = (hipStream_t)stream;
   float2 *stats = (float2 *)ws;
   const int units = batch * kv_heads;
-  const Grid g1 = plan_grid(batch * q_heads, units, tokens), g2 = plan_grid(units, units, tokens);
-  auto rowstats = g1.ws == 1 ? prefill_rowstats_kernel<1> : g1.ws == 2 ? prefill_rowstats_kernel<2> : prefill_rowstats_kernel<4>;
-  hipLaunchKernelGGL(rowstats, g1.blocks, dim3(kThreads), 0, st, q_prefill, k_prefill, q_heads, kv_heads, units, g1.nblk,
-                     g1.run, tokens, s2scale, stats);
-  auto colsum = g2.ws == 1 ? prefill_colsum_kernel<1> : g2.ws == 2 ? prefill_colsum_kernel<2> : prefill_colsum_kernel<4>;
-  hipLaunchKernelGGL(colsum, g2.blocks, dim3(kThreads), 0, st, q_prefill, k_prefill, q_heads, kv_heads, units, g2.nblk,
-                     g2.run, tokens, s2scale, (const float2 *)stats, scores);
+  const Grid g1 = plan_pass(batch * q_heads, units, 0, tokens), g2 = plan_pass(units, units, G, tokens);
+  if (g1.ws == 0) {
+    hipLaunchKernelGGL(short_rowstats_kernel, g1.blocks, dim3(64), 0, st, q_prefill, k_prefill, q_heads, kv_heads,
+                       batch * q_heads, tokens, s2scale, stats);
+  } else {
+    auto rowstats = g1.ws == 1 ? prefill_rowstats_kernel<1> : g1.ws == 2 ? prefill_rowstats_kernel<2> : prefill_rowstats_kernel<4>;
+    hipLaunchKernelGGL(rowstats, g1.blocks, dim3(kThreads), 0, st, q_prefill, k_prefill, q_heads, kv_heads, units, g1.nblk,
+                       g1.run, tokens, s2scale, stats);
+  }
+  if (g2.ws == 0) {
+    hipLaunchKernelGGL(short_colsum_kernel, g2.blocks, dim3(64), 0, st, q_prefill, k_prefill, q_heads, kv_heads, units,
+                       tokens, s2scale, (const float2 *)stats, scores);
+  } else {
+    auto colsum = g2.ws == 1 ? prefill_colsum_kernel<1> : g2.ws == 2 ? prefill_colsum_kernel<2> : prefill_colsum_kernel<4>;
+    hipLaunchKernelGGL(colsum, g2.blocks, dim3(kThreads), 0, st, q_prefill, k_prefill, q_heads, kv_heads, units, g2.nblk,
+                       g2.run, tokens, s2scale, (const float2 *)stats, scores);
+  }
   return check_launch("mikv_prefill_importance");
 }

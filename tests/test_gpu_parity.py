@@ -594,8 +594,21 @@ def test_prefill_importance_tile_edges(B, Hq, Hkv, T, grow):
         np.testing.assert_allclose(got.reshape(NH, T)[h].cpu().numpy(), ref, rtol=1e-4, atol=1e-6, err_msg=f"head {h}")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T", [
+    # either pass at the edges of the short kernels' ranges, the other one in
+    # either kernel, and tiles of 16 and blocks of 64 rows
+    *((1, 4, 4, T) for T in (1, 15, 16, 17, 64, 65, 191, 192, 193)),
+    *((1, 4, 1, T) for T in (16, 17, 72, 73)), *((1, 8, 1, T) for T in (52, 53)),
+    *((16, 64, 16, T) for T in (80, 81)), *((32, 32, 32, T) for T in (79, 81, 113, 192, 193, 257, 383, 385)),
+    *((64, 64, 16, T) for T in (112, 129, 191, 193, 335, 337)),
+    (1025, 64, 64, 3),   # more heads than one grid dimension takes
+])
+def test_prefill_importance_short_prompts(B, Hq, Hkv, T):
+    test_prefill_importance_tile_edges(B, Hq, Hkv, T, 0.0)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv", [(1, 2, 2), (1, 8, 1), (2, 96, 96), (8, 96, 96)])
-@pytest.mark.parametrize("T", [1, 31, 33, 65, 129, 257])
+@pytest.mark.parametrize("T", [1, 31, 33, 65, 129, 193, 249, 257])
 def test_prefill_importance_reads_no_row_past_the_prompt(B, Hq, Hkv, T):
     """q and k as the leading part of larger buffers whose following rows are
     NaN: the last tile of the last head must not see them (one, two and four
@@ -620,7 +633,7 @@ def test_prefill_importance_reads_no_row_past_the_prompt(B, Hq, Hkv, T):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv", [(1, 2, 2), (1, 8, 1), (2, 96, 96), (8, 96, 96)])
-@pytest.mark.parametrize("T", [5, 31, 33, 100, 257])
+@pytest.mark.parametrize("T", [5, 31, 33, 100, 193, 249, 257])
 def test_prefill_importance_masked_keys(B, Hq, Hkv, T):
     """Keys that every query scores -inf (an infinite channel, as a mask
     writes it) have probability 0: their scores are 0 and the others' those of
@@ -645,6 +658,7 @@ def test_prefill_importance_masked_keys(B, Hq, Hkv, T):
     # every key of a lane's half of a tile, or of a wave's share of the tiles
     (1, 2, 2, 8, slice(0, 4)), (1, 2, 2, 6, slice(0, 4)), (1, 4, 2, 100, slice(0, 32)), (2, 96, 96, 60, slice(0, 32)),
     (8, 96, 96, 7, slice(0, 4)), (1, 2, 2, 100, slice(40, 41)), (1, 2, 2, 300, slice(0, 1)),
+    (1, 2, 2, 200, slice(0, 36)), (2, 96, 96, 249, slice(0, 64)), (8, 96, 96, 249, slice(0, 4)),
 ])
 def test_prefill_importance_nan_keys_reach_every_later_query(B, Hq, Hkv, T, bad):
     """A NaN key makes the whole probability row of every later query NaN, so
