@@ -299,14 +299,18 @@ __host__ __device__ inline int64_t int2_v_byte(int64_t slot, int q) {
 // lane % 4, each with the 64 codes of its segment, channel 32 part + c at
 // bit 2c of w[0] | w[1] << 32): lane `part` gathers the 16-bit chunk `part`
 // of every segment's codes and writes bytes 8 part .. 8 part + 7.
+// (The codes as one 64-bit number: a choice between w[0] and w[1] becomes an
+// indexed array, which the compiler moves to LDS and addresses through the
+// dispatch packet in host memory, some 10 us for the first blocks of a launch.)
 __device__ inline void store_int2_v(uint8_t *head_base, int64_t slot, int part, const uint32_t w[2]) {
+  const uint64_t codes = (uint64_t)w[1] << 32 | w[0];
   uint32_t lo = 0u, hi = 0u;  // the lane's bytes 0-3 and 4-7
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     // round r: this lane sends chunk part ^ r of its own segment and
     // receives chunk `part` of segment part ^ r
     const int want = part ^ r;
-    const uint32_t mine = (((want & 2) ? w[1] : w[0]) >> (16 * (want & 1))) & 0xffffu;
+    const uint32_t mine = (uint32_t)(codes >> (16 * want)) & 0xffffu;
     const uint32_t c = r == 0 ? mine : (uint32_t)__shfl_xor((int)mine, r, 64);
     const int sh = 2 * (part ^ r);
 #pragma unroll
