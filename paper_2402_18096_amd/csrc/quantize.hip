@@ -295,69 +295,64 @@ __global__ __launch_bounds__(256) void place_kernel(Pools P, const uint16_t *k, 
   // --- quantize / store rows: 4 lanes per row --------------------------
   const int lane4 = tid & 3;
   const int ng = kHeadDim / P.group;
-  // row r of `m` tokens from order o0 on: keys, then values
-  auto load = [&](int r, int o0, int m, bool &is_v, int &t, int &slot, float x[32]) {
-    is_v = r >= m;
-    const int o = o0 + (is_v ? r - m : r);
-    t = s_token[o];
-    slot = s_slot[o];
-    const uint16_t *src = (is_v ? v : k) + ((int64_t)h * n + j0 + t) * kHeadDim + lane4 * 32;
-    load_row_segment(src, !is_v && balance ? balance + (int64_t)h * kHeadDim + lane4 * 32 : nullptr, x);
-  };
-  for (int r = r0; r < (P.evict ? 0 : 2 * cnt_lo); r += r_step) {
-    bool is_v;
-    int t, slot;
+  // Rows: retained-pool keys, then values, importance-pool keys, then values
+  // (evicted tokens have none), in one sequence, so that the rows of a short
+  // chunk are all under way at once (two loops, one per pool: 8 x 32 heads x 16
+  // tokens, INT8 + INT2, 12.4 -> 13.5 us).
+  const int rows_lo = 2 * cnt_lo;
+  for (int r = r0 + (P.evict ? rows_lo : 0); r < 2 * cnt; r += r_step) {
+    const bool hi = r >= rows_lo;
+    const int i = hi ? r - rows_lo : r, m = hi ? cnt_hi : cnt_lo;  // row of m tokens' keys and values
+    const bool is_v = i >= m;
+    const int o = (hi ? cnt_lo : 0) + (is_v ? i - m : i), t = s_token[o], slot = s_slot[o];
     float x[32];
-    load(r, 0, cnt_lo, is_v, t, slot, x);
+    load_row_segment((is_v ? v : k) + ((int64_t)h * n + j0 + t) * kHeadDim + lane4 * 32,
+                     !is_v && balance ? balance + (int64_t)h * kHeadDim + lane4 * 32 : nullptr, x);
     // every lane of a group must take part in the shuffles: no early exit
     const bool store = slot >= 0;
-    const int64_t row = (int64_t)h * P.cap_lo + (store ? slot : 0);
-    if (LO_BITS == 2 && is_v && P.v_tiled) {
-      // 2-bit values of a GQA cache go to the tiled layout, byte by byte
-      uint32_t w[2];
-      GroupParams gp = quantize_words<2>(x, P.group, w);
-      if (store) {
-        store_int2_v(P.lo_v + (int64_t)h * P.cap_lo * (kHeadDim / 4), slot, lane4, w);
-        if ((lane4 % (P.group / 32)) == 0)
-          P.lo_vp[row * ng + (lane4 * 32) / P.group] = (uint32_t)gp.a16 | ((uint32_t)gp.b16 << 16);
-      }
-    } else if (!is_v && P.lo_kb) {
-      // per-channel key: codes with its block's parameters (the block is
-      // complete: the placement above refused tokens of incomplete blocks)
-      if (store) {
-        uint32_t w[LO_BITS];
-        const int blk = (pos0 + j0 + t) / kKeyBlock;
-        encode_key_channels<LO_BITS>(x, P.lo_kb + ((int64_t)h * P.n_kblk + blk) * kHeadDim, lane4, w);
-        uint32_t *dst = reinterpret_cast<uint32_t *>(P.lo_k + row * (kHeadDim * LO_BITS / 8) + lane4 * (32 * LO_BITS / 8));
+    if (!hi) {
+      const int64_t row = (int64_t)h * P.cap_lo + (store ? slot : 0);
+      if (LO_BITS == 2 && is_v && P.v_tiled) {
+        // 2-bit values of a GQA cache go to the tiled layout, byte by byte
+        uint32_t w[2];
+        GroupParams gp = quantize_words<2>(x, P.group, w);
+        if (store) {
+          store_int2_v(P.lo_v + (int64_t)h * P.cap_lo * (kHeadDim / 4), slot, lane4, w);
+          if ((lane4 % (P.group / 32)) == 0)
+            P.lo_vp[row * ng + (lane4 * 32) / P.group] = (uint32_t)gp.a16 | ((uint32_t)gp.b16 << 16);
+        }
+      } else if (!is_v && P.lo_kb) {
+        // per-channel key: codes with its block's parameters (the block is
+        // complete: the placement above refused tokens of incomplete blocks)
+        if (store) {
+          uint32_t w[LO_BITS];
+          const int blk = (pos0 + j0 + t) / kKeyBlock;
+          encode_key_channels<LO_BITS>(x, P.lo_kb + ((int64_t)h * P.n_kblk + blk) * kHeadDim, lane4, w);
+          uint32_t *dst = reinterpret_cast<uint32_t *>(P.lo_k + row * (kHeadDim * LO_BITS / 8) + lane4 * (32 * LO_BITS / 8));
 #pragma unroll
-        for (int i = 0; i < LO_BITS; ++i) dst[i] = w[i];
-      }
-    } else {
-      uint8_t *dst = (is_v ? P.lo_v : P.lo_k) + row * (kHeadDim * LO_BITS / 8) + lane4 * (32 * LO_BITS / 8);
-      quantize_segment<LO_BITS>(x, P.group, lane4, dst, (is_v ? P.lo_vp : P.lo_kp) + row * ng + (lane4 * 32) / P.group,
-                                store);
-    }
-  }
-  for (int r = r0; r < 2 * cnt_hi; r += r_step) {
-    bool is_v;
-    int t, slot;
-    float x[32];
-    load(r, cnt_lo, cnt_hi, is_v, t, slot, x);
-    const bool store = slot >= 0;
-    const int64_t row = (int64_t)h * P.cap_hi + (store ? slot : 0);
-    if (HI_BITS == 16) {
-      if (store) {
-        uint4 *d4 = reinterpret_cast<uint4 *>((is_v ? P.hi_v : P.hi_k) + (row * kHeadDim + lane4 * 32) * 2);
-        uint32_t w[16];
-#pragma unroll
-        for (int c = 0; c < 16; ++c) w[c] = pack_f16x2(x[2 * c], x[2 * c + 1]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) d4[i] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
+          for (int i = 0; i < LO_BITS; ++i) dst[i] = w[i];
+        }
+      } else {
+        uint8_t *dst = (is_v ? P.lo_v : P.lo_k) + row * (kHeadDim * LO_BITS / 8) + lane4 * (32 * LO_BITS / 8);
+        quantize_segment<LO_BITS>(x, P.group, lane4, dst, (is_v ? P.lo_vp : P.lo_kp) + row * ng + (lane4 * 32) / P.group,
+                                  store);
       }
     } else {
-      uint8_t *dst = (is_v ? P.hi_v : P.hi_k) + row * (kHeadDim * HI_BITS / 8) + lane4 * (32 * HI_BITS / 8);
-      quantize_segment<HI_BITS>(x, P.group, lane4, dst, (is_v ? P.hi_vp : P.hi_kp) + row * ng + (lane4 * 32) / P.group,
-                                store);
+      const int64_t row = (int64_t)h * P.cap_hi + (store ? slot : 0);
+      if (HI_BITS == 16) {
+        if (store) {
+          uint4 *d4 = reinterpret_cast<uint4 *>((is_v ? P.hi_v : P.hi_k) + (row * kHeadDim + lane4 * 32) * 2);
+          uint32_t w[16];
+#pragma unroll
+          for (int c = 0; c < 16; ++c) w[c] = pack_f16x2(x[2 * c], x[2 * c + 1]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) d4[i] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
+        }
+      } else {
+        uint8_t *dst = (is_v ? P.hi_v : P.hi_k) + row * (kHeadDim * HI_BITS / 8) + lane4 * (32 * HI_BITS / 8);
+        quantize_segment<HI_BITS>(x, P.group, lane4, dst, (is_v ? P.hi_vp : P.hi_kp) + row * ng + (lane4 * 32) / P.group,
+                                  store);
+      }
     }
   }
   if (commit && tid == 0) {  // (every thread read the counts before the barriers above)
