@@ -207,14 +207,19 @@ __device__ inline void pack32(Code code, uint32_t w[BITS]) {
 // encode() of the 32 values of one lane's segment, packed LSB-first into
 // w[BITS], without a divide per value: the quotient (x - beta) / alpha is
 // estimated as x * r - beta * r with r = fl(1 / alpha), one fused multiply-add.
-// With Q the exact quotient, the estimate is within 2^-22 |Q| + 2^-22
-// |beta r| of Q and encode()'s own within 2^-22 |Q|; quotients past the code
-// range clamp to the same code, so |Q| <= 2^BITS matters.  The rounded code can
-// differ only where a half-integer lies between the two, so where an
-// estimate is within 2^-20 (|beta r| + 2^BITS + 1) of a half-integer the wave
-// packs again from the true divide; the codes are those of encode()
-// bit for bit.  About seven VALU instructions per value, where a relative
-// test per value, a clamp, a conversion and a shift took some twenty.
+// With Q the exact quotient, the estimate is within 2^-23 |Q| + 2^-24 |beta r|
+// of Q (the error of r scales the whole difference; that of beta r, and the last
+// rounding, are half an ulp each) and encode()'s own within 2^-23 |Q|; quotients
+// past the code range clamp to the same code, so |Q| <= 2^BITS matters.  The
+// rounded code can differ only where a half-integer lies between the two, so
+// where an estimate is within 2^-22 (|beta r| + 2^BITS + 1) of a half-integer the
+// wave packs again from the true divide; the codes are those of encode()
+// bit for bit (the furthest that differed in 5e8 quotients at and beside
+// half-integers was at 2^-23.2 of that scale).  The first pass takes about seven
+// VALU instructions per value.  The second one is taken by the wave (2048 values)
+// for exact ties, which Gaussian fp16 rows hold in 25-60 % of the waves, and for
+// near ones: of balanced rows, whose values are no fp16 numbers, 31 % at 8 bits (with
+// a slack of 2^-20: 77 %), 2 % at 4 and 0.5 % at 2 bits.
 template <int BITS>
 __device__ inline void encode32(const float x[32], const GroupParams &p, uint32_t w[BITS]) {
   const float top = (float)((1 << BITS) - 1);
@@ -228,7 +233,7 @@ __device__ inline void encode32(const float x[32], const GroupParams &p, uint32_
         return __builtin_amdgcn_fmed3f(t, 0.0f, top);
       },
       w);
-  if (__ballot(!(far <= 0.5f - 0x1p-20f * (fabsf(nb) + (top + 2.0f))))) {
+  if (__ballot(!(far <= 0.5f - 0x1p-22f * (fabsf(nb) + (top + 2.0f))))) {
     pack32<BITS>(
         [&](int c) { return zero ? 0.0f : __builtin_amdgcn_fmed3f(rintf((x[c] - p.b) / p.a), 0.0f, top); }, w);
   }

@@ -65,6 +65,33 @@ def test_quantize_rows_bit_exact(bits, group, balanced):
     np.testing.assert_array_equal(p[..., 1], b_ref)
 
 
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("spread", [0.0, 1.0, 30.0])
+def test_quantize_rows_bit_exact_beside_half_integers(bits, spread):
+    """Quotients at half-integers and up to four fp32 ulps beside them (a
+    balancer per row makes the inputs any fp32 number), groups whose offset is
+    0, one and thirty times their range: the estimate through the reciprocal
+    lands on the wrong side of many of them, and each of those has to be seen."""
+    dev = _dev()
+    rng = np.random.default_rng(bits)
+    rows, group, top = 8192, 32, (1 << bits) - 1
+    a = (2.0 ** rng.uniform(-9, 1, (rows, 4, 1))).astype(np.float16).astype(np.float64)
+    b = (spread * top * a * rng.uniform(-1, 1, a.shape)).astype(np.float16).astype(np.float64) + 0.0   # (no -0)
+    x = ((np.floor(rng.random((rows, 4, group)) * top) + 0.5) * a + b).astype(np.float32)
+    for _ in range(4):
+        x = np.nextafter(x, np.where(rng.random(x.shape) < 0.5, x, np.float32(np.inf) * rng.choice([-1, 1], x.shape)).astype(np.float32))
+    x[..., 0], x[..., 1] = b[..., 0], (b + top * a)[..., 0]
+    x = x.reshape(rows, 128)
+    codes = torch.empty(rows, 128 * bits // 8, dtype=torch.uint8, device=dev)
+    params = torch.empty(rows, 128 // group, 2, dtype=torch.int16, device=dev)
+    sign = torch.from_numpy(np.where(x < 0, -1.0, 1.0).astype(np.float16).view(np.int16)).to(dev).view(torch.float16)
+    mikv.mikv_quantize_rows(sign, bits, group, codes, params, torch.from_numpy(np.abs(x)).to(dev), 1)
+    torch.cuda.synchronize()
+    c_ref, a_ref, b_ref = oracle.quantize(x, bits, group)
+    np.testing.assert_array_equal(params.cpu().numpy().view(np.uint16), np.stack([a_ref, b_ref], -1))
+    np.testing.assert_array_equal(codes.cpu().numpy(), oracle.pack(c_ref, bits))
+
+
 def test_quantize_rows_empty_is_noop():
     dev = _dev()
     codes = torch.zeros(1, 32, dtype=torch.uint8, device=dev)
