@@ -123,6 +123,27 @@ def test_balancer_bit_exact(G):
     np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), ref.view(np.uint32))
 
 
+def test_balancer_of_a_prompt_larger_than_the_last_level_cache():
+    """Past 256 MiB of queries and keys the rows are read with non-temporal
+    loads: first, middle and last head, with a ragged last chunk."""
+    dev = _dev()
+    B, Hkv, G, T = 3, 8, 4, 8801    # 270 MB
+    g = torch.Generator(device=dev)
+    g.manual_seed(1)
+    q = torch.randn(B, Hkv * G, T, 128, generator=g, device=dev).half()
+    k = torch.randn(B, Hkv, T, 128, generator=g, device=dev).half()
+    assert 256 << 20 < 2 * (q.numel() + k.numel()) < 300 << 20
+    for h in (0, B * Hkv - 1):      # the maxima in the last row
+        k.view(-1, T, 128)[h, -1, 3] = 50.0
+        q.view(-1, T, 128)[h * G + G - 1, -1, 5] = -60.0
+    out = torch.empty(B, Hkv, 128, dtype=torch.float32, device=dev)
+    mikv.mikv_balance_channels(q, k, out)
+    torch.cuda.synchronize()
+    for h in (0, B * Hkv // 2, B * Hkv - 1):
+        ref = oracle.balancer(np16(q.view(1, 1, -1, G, T, 128)[:, :, h]), np16(k.view(1, 1, -1, T, 128)[:, :, h]))
+        np.testing.assert_array_equal(out.view(-1, 128)[h].cpu().numpy().view(np.uint32), ref.reshape(128).view(np.uint32))
+
+
 # -- selection -------------------------------------------------------------------------
 
 @pytest.mark.parametrize("L,k,W", [(1000, 150, 32), (5000, 900, 128), (300, 0, 10), (300, 500, 10), (64, 10, 100),
@@ -140,6 +161,24 @@ def test_select_prefill_matches_oracle(L, k, W):
     got = mask.cpu().numpy().astype(bool)
     for h in range(H):
         np.testing.assert_array_equal(got[h], oracle.select(sc[h], None, L, k, W, initial=True))
+
+
+def test_select_prefill_more_heads_than_one_launch():
+    dev = _dev()
+    H, L = (1 << 20) + 3, 4
+    g = torch.Generator(device=dev)
+    g.manual_seed(2)
+    sc = torch.rand(H, L, generator=g, device=dev).argsort(1).float()   # no ties
+    mask = torch.full((H, L), 7, dtype=torch.uint8, device=dev)
+    mikv.mikv_select_prefill(sc, 1, 1, mask)
+    torch.cuda.synchronize()
+    want = torch.zeros(H, L, dtype=torch.uint8, device=dev)
+    want[:, 3] = 1                                        # the window
+    want.scatter_(1, sc[:, :3].argmax(1, keepdim=True), 1)
+    assert torch.equal(mask, want)
+    for h in (0, (1 << 20) - 1, 1 << 20, H - 1):
+        np.testing.assert_array_equal(mask[h].cpu().numpy().astype(bool),
+                                      oracle.select(sc[h].cpu().numpy(), None, L, 1, 1, initial=True))
 
 
 @pytest.mark.parametrize("L,k,W", [(4096, 900, 1), (4097, 1, 1), (16384, 16000, 7), (16385, 5000, 0),
