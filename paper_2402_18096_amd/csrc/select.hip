@@ -26,11 +26,15 @@ __global__ __launch_bounds__(kSel) __attribute__((amdgpu_waves_per_eu(5))) void 
 // exponents meet in few bins) at one or two blocks per CU.  Against 256 threads
 // that read the scores again for eight 8-bit passes: 128 heads x 32768 tokens
 // 277 -> 46 us, 1280 x 8192 175 -> 54 us, 4 x 512 39 -> 5.4 us.
-constexpr int kPre = 1024;        // threads
+// Once the score is known the next digit starts at the highest bit that a
+// position of this prompt can have.  Blocks have 1024 threads, or 256 for
+// prompts of up to 1024 tokens with heads enough to fill the chip, where four
+// times the blocks fit a CU (8192 heads x 16
+// tokens, all scores equal: 157 -> 27 us; 93 with the 8-bit passes).
 constexpr int kDigitBits = 11;
 constexpr int kBins = 1 << kDigitBits;
 
-template <int ITEMS>
+template <int kPre, int ITEMS>
 __global__ __launch_bounds__(kPre) void select_prefill_kernel(const float *scores, int length, int k_heavy, int window,
                                                               uint8_t *hi_mask) {
   __shared__ uint32_t s_hist[kBins];
@@ -64,7 +68,8 @@ __global__ __launch_bounds__(kPre) void select_prefill_kernel(const float *score
   // the bits of the prefix that earlier digits fixed.
   uint64_t prefix = 0, known = 0;
   uint32_t rank = (uint32_t)n_dem;
-  for (int shift = 64 - kDigitBits;; shift = shift > kDigitBits ? shift - kDigitBits : 0) {
+  const int pos_bits = thr > 1 ? 32 - __clz(thr - 1) : 0;  // positions are below 2^pos_bits
+  for (int shift = 64 - kDigitBits;;) {
     for (int b = tid; b < kBins; b += kPre) s_hist[b] = 0u;
     __syncthreads();
     each([&](uint32_t o, uint32_t i) {
@@ -72,9 +77,12 @@ __global__ __launch_bounds__(kPre) void select_prefill_kernel(const float *score
       if (((key ^ prefix) & known) == 0) atomicAdd(&s_hist[(uint32_t)(key >> shift) & (kBins - 1)], 1u);
     });
     __syncthreads();
-    // the bin that holds the rank: two bins per thread, an inclusive scan
-    const uint32_t c0 = s_hist[2 * tid], c1 = s_hist[2 * tid + 1];
-    uint32_t incl = c0 + c1;
+    // the bin that holds the rank: a few bins per thread, an inclusive scan
+    constexpr int PER = kBins / kPre;
+    uint32_t c[PER], incl = 0u;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) incl += c[e] = s_hist[PER * tid + e];
+    const uint32_t own = incl;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const uint32_t up = __shfl_up(incl, o, 64);
@@ -83,12 +91,19 @@ __global__ __launch_bounds__(kPre) void select_prefill_kernel(const float *score
     if (lane == 63) s_wave[wave] = incl;
     __syncthreads();
     for (int w = 0; w < wave; ++w) incl += s_wave[w];
-    const uint32_t before = incl - c0 - c1;
+    uint32_t before = incl - own;
     if (before < rank && rank <= incl) {  // one thread
-      const bool second = rank > before + c0;
-      s_pick[0] = 2 * tid + (second ? 1 : 0);
-      s_pick[1] = rank - before - (second ? c0 : 0);
-      s_pick[2] = second ? c1 : c0;
+      bool found = false;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        if (!found && rank <= before + c[e]) {
+          found = true;
+          s_pick[0] = PER * tid + e;
+          s_pick[1] = rank - before;
+          s_pick[2] = c[e];
+        }
+        if (!found) before += c[e];
+      }
     }
     __syncthreads();
     prefix |= (uint64_t)s_pick[0] << shift;  // (the last digit's upper bits are known ones again)
@@ -98,6 +113,8 @@ __global__ __launch_bounds__(kPre) void select_prefill_kernel(const float *score
       prefix |= ((uint64_t)1 << shift) - 1;  // the whole bin leaves
       break;
     }
+    const int next = shift - kDigitBits;
+    shift = max(0, shift <= 32 ? min(next, pos_bits - kDigitBits) : next);
   }
   const uint64_t cut = prefix;
   each([&](uint32_t o, uint32_t i) { mask[i] = ((((uint64_t)o << 32) | i) <= cut) ? 0 : 1; });
@@ -231,12 +248,14 @@ extern "C" int mikv_select_prefill(const float *scores, int32_t n_heads, int32_t
   if (!scores || !hi_mask) return set_error(MIKV_ERR_INVALID_ARG, "mikv_select_prefill: NULL pointer");
   if (n_heads < 1 || length < 1 || k_heavy < 0 || window < 0)
     return set_error(MIKV_ERR_INVALID_ARG, "mikv_select_prefill: bad sizes");
-  auto kernel = length <= 4 * kPre    ? select_prefill_kernel<4>
-                : length <= 16 * kPre ? select_prefill_kernel<16>
-                                      : select_prefill_kernel<32>;
+  const int threads = n_heads >= 512 && length <= 1024 ? 256 : 1024;
+  auto kernel = threads == 256         ? select_prefill_kernel<256, 4>
+                : length <= 4 * 1024  ? select_prefill_kernel<1024, 4>
+                : length <= 16 * 1024 ? select_prefill_kernel<1024, 16>
+                                      : select_prefill_kernel<1024, 32>;
   constexpr int kMost = 1 << 20;  // heads per launch: a grid's threads stay below 2^32
   for (int64_t h0 = 0; h0 < n_heads; h0 += kMost)
-    hipLaunchKernelGGL(kernel, dim3((int)std::min<int64_t>(kMost, n_heads - h0)), dim3(kPre), 0, (hipStream_t)stream,
+    hipLaunchKernelGGL(kernel, dim3((int)std::min<int64_t>(kMost, n_heads - h0)), dim3(threads), 0, (hipStream_t)stream,
                        scores + h0 * length, length, k_heavy, window, hi_mask + h0 * length);
   return check_launch("mikv_select_prefill");
 }

@@ -163,6 +163,23 @@ def test_select_prefill_matches_oracle(L, k, W):
         np.testing.assert_array_equal(got[h], oracle.select(sc[h], None, L, k, W, initial=True))
 
 
+@pytest.mark.parametrize("H,L,k,W", [(512, 1024, 300, 16), (512, 1025, 300, 0), (511, 1024, 300, 16), (600, 1, 0, 0),
+                                     (600, 2, 1, 0), (700, 257, 100, 3)])
+def test_select_prefill_many_short_heads(H, L, k, W):
+    """Both block sizes, with ties that only the position digits tell."""
+    dev = _dev()
+    rng = np.random.default_rng(H + L)
+    sc = (rng.integers(0, 3, (H, L)) / 4).astype(np.float32)
+    sc[::3] = 0.25
+    sc[1::3] = rng.random((len(sc[1::3]), L))
+    mask = torch.empty(H, L, dtype=torch.uint8, device=dev)
+    mikv.mikv_select_prefill(torch.from_numpy(sc).to(dev), k, W, mask)
+    torch.cuda.synchronize()
+    got = mask.cpu().numpy().astype(bool)
+    for h in (*range(9), H // 2, H - 2, H - 1):
+        np.testing.assert_array_equal(got[h], oracle.select(sc[h], None, L, k, W, initial=True))
+
+
 def test_select_prefill_more_heads_than_one_launch():
     dev = _dev()
     H, L = (1 << 20) + 3, 4
