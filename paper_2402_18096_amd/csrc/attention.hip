@@ -1513,13 +1513,17 @@ __device__ inline void merge_output(const AttnArgs &A, int qh0, int nc, const fl
   const int i = G <= 4 ? __builtin_amdgcn_readfirstlane(wave % G) : (threadIdx.x / 32) % G;
   const int s = G <= 4 ? (wave / G) * 2 + (lane >> 5) : threadIdx.x / (32 * G);
   const float *rec = A.partials + (int64_t)(qh0 + i) * nc * kRec;
+  // (through copies that the compiler cannot trace back to M and inv: it would
+  // make indexed arrays of the choices, in scratch, or in LDS addressed
+  // through the dispatch packet in host memory)
   float Mi = M[0], invi = inv[0];
 #pragma unroll
-  for (int j = 1; j < G; ++j)
-    if (i == j) {
-      Mi = M[j];
-      invi = inv[j];
-    }
+  for (int j = 1; j < G; ++j) {
+    float Mj = M[j], invj = inv[j];
+    asm("" : "+v"(Mj), "+v"(invj));
+    Mi = i == j ? Mj : Mi;
+    invi = i == j ? invj : invi;
+  }
   float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   // RB records per thread and batch, all loaded before any is used (a
   // missing record reads record 0 and gets weight 0): one memory round trip
