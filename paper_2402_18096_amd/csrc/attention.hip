@@ -1812,7 +1812,16 @@ Plan make_plan(const mikv_cache *c, int length, bool size_bound = false) {
   // -> 23.3; 1 x 32/4 x 32768 (464 records) 55.9 -> 51.4.
   const int64_t base = NH * (p.nc_hi + p.nc_lo);
   const int G = group_size_of(c);
+  // With codes in both pools and 3 bits or more in the retained one (at G = 8,
+  // where a wave has the most arithmetic, also for fp16 + INT4 and INT8) two waves that
+  // share a SIMD always lose: one while the long chunks leave SIMDs idle (at G = 8
+  // three to four SIMDs, since a full one doubles some), else the long
+  // chunks (us with the importance update, long, two waves, this: 4 x 64/8 x
+  // 4000, INT8 + INT3 40.3, 51.7, 38.6; 4 x 32/8 x 4000 24.8, 28.5, 22.3).
+  const bool arith = c->lo_bits != 2 && (c->hi_bits != 16 || (G >= 8 && c->lo_bits >= 4));
+  const int64_t one = G >= 8 ? kSimds * 3 / 4 : kSimds;
   const int64_t fit = G < 4 || base >= kFewWaves            ? 0
+                      : arith                               ? (base < one ? one : 0)
                       : G >= 8                              ? kFewWaves
                       : base < kSimds                       ? kSimds
                       : c->hi_bits == 16 && c->lo_bits == 2 ? 0

@@ -511,6 +511,12 @@ def test_lockstep_gqa8():
     dict(batch=8, q_heads=32, kv_heads=8, context=2000, window=64),
     dict(batch=16, q_heads=32, kv_heads=8, context=2000, window=64, hi_bits=8),
     dict(batch=16, q_heads=32, kv_heads=8, context=2000, window=64),
+    # codes in both pools: 64-token importance-pool chunks up to three waves to
+    # four SIMDs, whole ones above; fp16 + INT4 likewise at G = 8
+    dict(batch=2, q_heads=64, kv_heads=8, context=998, hi_bits=8, lo_bits=3),
+    dict(batch=4, q_heads=64, kv_heads=8, context=2500, hi_bits=8, lo_bits=4),
+    dict(batch=2, q_heads=64, kv_heads=8, context=998, lo_bits=4),
+    dict(batch=4, q_heads=32, kv_heads=8, context=1400, hi_bits=8, lo_bits=8),
     # some 180 records per head: several rounds of the output merge, which the
     # fused step does in a block per query head
     dict(batch=1, q_heads=8, kv_heads=1, context=16001),
