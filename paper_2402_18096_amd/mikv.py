@@ -132,7 +132,7 @@ def _require(t: torch.Tensor, dtype, shape=None, name="tensor"):
         raise MikvError(f"{name}: expected {dtype}, got {t.dtype}")
     if not t.is_cuda:
         raise MikvError(f"{name}: must be a device tensor")
-    if shape is not None and t.shape != shape:
+    if shape is not None and t.shape != shape and tuple(t.shape) != tuple(shape):
         raise MikvError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
 
 

@@ -4,6 +4,7 @@ declares, and rejects bad arguments on the host before launching anything
 import ctypes
 import os
 import re
+import types
 
 import pytest
 import torch  # noqa: F401  (loads the HIP runtime libmikv.so links against)
@@ -272,3 +273,13 @@ def test_resident_budget_fits_the_last_level_cache():
     finally:
         mikv.mikv_set_resident_bytes(default)
     assert mikv.mikv_resident_bytes() == default
+
+
+def test_binding_takes_an_expected_shape_as_any_sequence():
+    """A torch.Size equals a tuple, never a list."""
+    t = types.SimpleNamespace(dtype=torch.float32, is_cuda=True, shape=torch.Size((2, 3)))
+    for shape in ((2, 3), [2, 3], torch.Size((2, 3))):
+        mikv._require(t, torch.float32, shape)
+    for shape in ((3, 2), [2], (2, 3, 1)):
+        with pytest.raises(mikv.MikvError):
+            mikv._require(t, torch.float32, shape)
