@@ -174,8 +174,10 @@ int mikv_balance_channels(const uint16_t *q_prefill, const uint16_t *k_prefill, 
  *   scores[b, h, j] = sum_{g in group(h)} sum_{i = j}^{T-1} softmax_i(scale * q[b, g, i] . k[b, h, :])_j
  * where group(h) are the Hq / Hkv query heads sharing KV head h.  Logits are
  * fp16 x fp16 products accumulated in fp32 on the matrix cores; the sums
- * are fp32 in an order that the sizes fix (32 partial sums per key over the
- * queries of every 32nd column of the tiles, then a tree), so results are
+ * are fp32 in an order that the sizes fix (per key and wave 32 partial sums over
+ * the queries of every 32nd column of the tiles, then a tree, then the one, two
+ * or four waves that share the key's queries in turn; short prompts four partial
+ * sums over every fourth group of four queries), so results are
  * reproducible run to run but not bit-identical to another summation order.
  *   q_prefill fp16 [B, Hq, T, 128]; k_prefill fp16 [B, Hkv, T, 128], both
  *             16-byte aligned (the prompt's keys as computed, before any

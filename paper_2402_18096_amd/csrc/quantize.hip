@@ -211,8 +211,9 @@ __device__ inline int wave_count(const int32_t *counts, int n) {
 // The rows are quantized pool by pool, keys then values, so that a wave runs
 // one format (a wave over neighbouring tokens nearly always held both pools,
 // and ran both encoders for all its rows).  Bound: the stream of fp16 rows and
-// codes, now that a value costs some ten VALU instructions (encode32): 1280
-// heads x 8192 tokens, INT8 + INT2 2254 -> 1637 us (4.2 TB/s of rows read and
+// codes, and in part the encoding, some ten VALU instructions per value and as
+// many again with divides in the waves that pack twice (encode32): 1280
+// heads x 8192 tokens, INT8 + INT2 2254 -> 1480 us (4.7 TB/s of rows read and
 // codes written), 128 x 32768, fp16 + INT2 661 -> 593 us (4.6 TB/s), 128 x
 // 16384, GQA 535 -> 338 us.
 template <int HI_BITS, int LO_BITS>

@@ -181,7 +181,7 @@ __device__ inline void load_hi_segment(const SelArgs &A, const uint8_t *rows, co
 
 // Eq. 1 codes at LO_BITS of 32 decoded channels (a group spans group/32
 // lanes): the packed little-endian words and the group parameters.  TIGHT: one
-// divide per code instead of encode32, whose rare second pass over the divides
+// divide per code instead of encode32, whose second pass over the divides
 // makes a kernel held to 96 registers spill (select_kernel, 1280 heads 10.0 ->
 // 11.4 us); in the fused finalize it shortens the re-rank's chain (256 heads
 // INT8 + INT4 10.3 -> 9.1 us per launch, 4 heads x 512 tokens 292 -> 277 us per
