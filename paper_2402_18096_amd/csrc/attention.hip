@@ -1594,6 +1594,7 @@ void attn_finalize_kernel(AttnArgs A, int accumulate, int tiles_hi, int tiles_lo
   const int h = blockIdx.x, c = blockIdx.y;  // heads fastest: every head's merges are dispatched first
   const int qh0 = h * G;  // = b * q_heads + kv head * G
   const int nc = A.nc_hi + A.nc_lo;
+  if constexpr (G < 4) merges = 1;  // (as merge_blocks has it, known to the compiler)
   if (c < merges) {  // a merge holds no tile
     merge_group<G>(A, qh0, nc, c, merges);
     return;
@@ -1644,6 +1645,7 @@ __global__ __launch_bounds__(kBlock) void finalize_select_kernel(AttnArgs A, int
   const int b = h / A.kv_heads, kvh = h % A.kv_heads;
   const int qh0 = b * A.q_heads + kvh * G;
   const int nc = A.nc_hi + A.nc_lo;
+  if constexpr (G < 4) merges = 1;  // (as merge_blocks has it, known to the compiler)
   if (c >= 1 && c <= merges) {  // a merge holds no tile
     merge_group<G>(A, qh0, nc, c - 1, merges);
     return;
